@@ -376,7 +376,9 @@ ss_status ss_hop_distances(const uint32_t* row_off, const uint32_t* col, uint32_
  *   velocity closing speed in tiles per step (>= 1); radius in tiles;
  *   out      [n_agents] out (may alias d_action);
  *   workspace  ss_interaction_distances_workspace(n_agents) bytes of device
- *            memory, owned by the caller, no initialisation needed.
+ *            memory, owned by the caller, no initialisation needed.  With less
+ *            (but at least 4 n_agents bytes) or without 16-byte alignment the
+ *            call compares all pairs, which takes longer for many agents.
  * Device memory of the current device, owned by the caller; queued on
  * `stream`, returns without waiting.  SS_ERR_ARG for NULL, too small or
  * non-device arguments or velocity 0, SS_ERR_HIP if a launch fails. */
@@ -388,15 +390,15 @@ ss_status ss_interaction_distances(const int32_t* pos_xy, const uint32_t* d_acti
 
 /* The same computation for callers that cannot allocate device memory (code
  * under HIP graph capture, tight serving loops, harnesses that forbid
- * hipMalloc): the partial minima live in a static device array of the
- * library instead of a workspace, so the call allocates nothing.  At most
- * 1,048,576 agents (SS_ERR_ARG beyond, nothing queued).  The array holds
- * 4 MiB on each device the library runs on until the process ends; its
- * device address is looked up on the first call on a device.  Every call on
- * one device shares that array and clears it on `stream` before use: calls
- * whose work overlaps on one device (other streams, other threads) race and
- * give unspecified results.  Other arguments, errors and results as
- * ss_interaction_distances. */
+ * hipMalloc): a static device array of the library serves as workspace, so the
+ * call allocates nothing.  At most 1,048,576 agents (SS_ERR_ARG beyond, nothing
+ * queued); beyond about 120,000 the workspace would not fit the array, and the
+ * call compares all pairs.  The array holds 4 MiB on each device the library
+ * runs on until the process ends; its device address is looked up on the first
+ * call on a device that needs it.  Every call on one device shares that array:
+ * calls whose work overlaps on one device (other streams, other threads) race
+ * and give unspecified results (but no access outside the arrays).  Other
+ * arguments, errors and results as ss_interaction_distances. */
 ss_status ss_interaction_distances_static(const int32_t* pos_xy, const uint32_t* d_action,
                                           uint32_t n_agents, uint32_t velocity, uint32_t radius,
                                           uint32_t* out, void* stream);

@@ -42,12 +42,11 @@
 // ss_interaction_distances (interaction-involved simulations): D =
 // min(D_action, floor(max(0, isqrt(d2) - radius) / velocity)) with d2 the
 // squared distance to the nearest other agent on an integer tile grid.
-//   k_pair_min  all pairs, 256 agents per workgroup against a slice of the
-//               others staged through LDS as packed 16-bit (x, y); per pair a
-//               packed 16-bit subtract and a 16-bit dot product give dx^2 +
-//               dy^2 exactly; one atomic min per agent and slice.
-//   k_pair_fin  integer square root, radius, velocity and the min with
-//               D_action.
+//   k_pair      all pairs in one launch (few agents): per pair a packed 16-bit
+//               subtract and a 16-bit dot product give dx^2 + dy^2 exactly.
+//   k_near_*    many agents: sorted into cells, each looks only at the cells
+//               about it (50,000 agents: 206 us by all pairs, 40 us; 200,000:
+//               3,330 and 52 us).
 // Both are plain integer ALU work (no contraction), so no MFMA.
 #include "scalesim.h"
 #include "ss_internal.h"
@@ -480,9 +479,6 @@ __global__ void __launch_bounds__(kBfsThreads) k_bfs(BfsArgs A) {
 // Interaction distances
 // ---------------------------------------------------------------------------
 
-constexpr int kPairThreads = 256;            // agents i per workgroup
-constexpr int kPairTile = 256;               // agents j staged per LDS round
-
 typedef short short2_t __attribute__((ext_vector_type(2)));
 
 // Squared distance of two grid points held as packed 16-bit (x, y): one packed
@@ -490,60 +486,17 @@ typedef short short2_t __attribute__((ext_vector_type(2)));
 // differences nor the sum of squares overflow).  The dot product is written
 // in its three-operand form with a zero addend; the compiler's two-operand
 // form would need a register cleared before every pair.
-__device__ __forceinline__ unsigned dist2(short2_t a, short2_t b) {
-    const short2_t d = a - b;
+__device__ __forceinline__ unsigned dist2(unsigned a, unsigned b) {
+    const short2_t d = __builtin_bit_cast(short2_t, a) - __builtin_bit_cast(short2_t, b);
     int r;
     asm("v_dot2_i32_i16 %0, %1, %1, 0" : "=v"(r) : "v"(d));
     return (unsigned)r;
 }
 
-// Partial minimum of the squared distance from each agent i of the workgroup
-// to the agents j of slice [j_lo, j_hi), excluding j = i, into d2min[i].
-__global__ void __launch_bounds__(kPairThreads) k_pair_min(const int* __restrict__ pos,
-                                                           unsigned n, unsigned slice,
-                                                           unsigned* __restrict__ d2min) {
-    __shared__ __attribute__((aligned(16))) short2_t s_p[kPairTile];
-    const unsigned i = blockIdx.x * kPairThreads + threadIdx.x;
-    const unsigned j_lo = blockIdx.y * slice, j_hi = min(j_lo + slice, n);
-    short2_t pi = {0, 0};
-    if (i < n) pi = short2_t{(short)pos[2 * i], (short)pos[2 * i + 1]};
-    unsigned best = kNone;
-    // the next tile's position is loaded while the current tile is compared
-    int2 nxt = make_int2(0, 0);
-    if (j_lo + threadIdx.x < j_hi)
-        nxt = make_int2(pos[2 * (j_lo + threadIdx.x)], pos[2 * (j_lo + threadIdx.x) + 1]);
-    for (unsigned j0 = j_lo; j0 < j_hi; j0 += kPairTile) {
-        const unsigned j = j0 + threadIdx.x;
-        if (j < j_hi) s_p[threadIdx.x] = short2_t{(short)nxt.x, (short)nxt.y};
-        __syncthreads();
-        if (j + kPairTile < j_hi) nxt = make_int2(pos[2 * (j + kPairTile)], pos[2 * (j + kPairTile) + 1]);
-        const unsigned cnt = min((unsigned)kPairTile, j_hi - j0);
-        if (i - j0 < cnt) {                  // this tile holds i itself: skip the self pair
-            for (unsigned k = 0; k < cnt; ++k)
-                if (j0 + k != i) best = min(best, dist2(pi, s_p[k]));
-        } else if (cnt == kPairTile) {
-            // four positions per 16-byte LDS read (a broadcast: every lane reads
-            // the same address), so the LDS issues a quarter of the reads
-            const uint4* q = reinterpret_cast<const uint4*>(s_p);
-#pragma unroll 8
-            for (unsigned k = 0; k < kPairTile / 4; ++k) {
-                const uint4 v = q[k];
-                best = min(best, dist2(pi, __builtin_bit_cast(short2_t, v.x)));
-                best = min(best, dist2(pi, __builtin_bit_cast(short2_t, v.y)));
-                best = min(best, dist2(pi, __builtin_bit_cast(short2_t, v.z)));
-                best = min(best, dist2(pi, __builtin_bit_cast(short2_t, v.w)));
-            }
-        } else {
-            for (unsigned k = 0; k < cnt; ++k) best = min(best, dist2(pi, s_p[k]));
-        }
-        __syncthreads();
-    }
-    if (i < n && best != kNone) atomicMin(&d2min[i], best);
-}
-
-__global__ void __launch_bounds__(256) k_pair_init(unsigned* d2min, unsigned n) {
-    const unsigned i = blockIdx.x * 256u + threadIdx.x;
-    if (i < n) d2min[i] = kNone;
+// A position as packed 16-bit (x, y), each in [0, 2^15) whatever the caller
+// passed (so that every index derived from it stays in its array).
+__device__ __forceinline__ unsigned pack_pos(int x, int y) {
+    return ((unsigned)x & 0x7FFFu) | (((unsigned)y & 0x7FFFu) << 16);
 }
 
 __device__ __forceinline__ unsigned isqrt_u32(unsigned x) {
@@ -553,19 +506,653 @@ __device__ __forceinline__ unsigned isqrt_u32(unsigned x) {
     return r;
 }
 
-__global__ void __launch_bounds__(256) k_pair_fin(const unsigned* __restrict__ d2min,
-                                                  const unsigned* __restrict__ d_action,
-                                                  unsigned n, unsigned velocity, unsigned radius,
-                                                  unsigned* __restrict__ out) {
-    const unsigned i = blockIdx.x * 256u + threadIdx.x;
-    if (i >= n) return;
-    unsigned d = d_action[i];
-    const unsigned m = d2min[i];
-    if (m != kNone) {
-        const unsigned dist = isqrt_u32(m);
-        d = min(d, (dist > radius ? dist - radius : 0u) / velocity);
+// The result of an agent whose nearest other agent is at squared distance m
+// (kNone: there is none) and whose current action ends in d steps.
+__device__ __forceinline__ unsigned interaction_of(unsigned m, unsigned d, unsigned velocity,
+                                                   unsigned radius) {
+    if (m == kNone) return d;
+    const unsigned dist = isqrt_u32(m);
+    return min(d, (dist > radius ? dist - radius : 0u) / velocity);
+}
+
+// All pairs in one launch: a workgroup takes kOwn agents (one per lane, 64 /
+// kOwn lanes for each of them), its kPairWaves waves take the others in turn,
+// 64 at a time staged through the wave's own LDS as packed positions, of which
+// an agent's lanes take equal parts, and the minima meet in LDS.  Bound by the
+// vector ALU (2.5 instructions a pair), so by how evenly the workgroups cover
+// the 256 CUs: see pair_launch.
+constexpr int kPairWaves = 16;
+
+struct PairArgs {
+    const int* pos;                   // [n][2]
+    const unsigned* d_action;         // [n] (may be `out`)
+    unsigned* out;                    // [n]
+    unsigned n, velocity, radius;
+};
+
+template <unsigned kOwn>
+__global__ void __launch_bounds__(64 * kPairWaves) k_pair(PairArgs A) {
+    constexpr unsigned kParts = 64 / kOwn, kPart = 64 / kParts;   // others per lane and group
+    __shared__ uint4 s_pos[kPairWaves][2][16];
+    __shared__ unsigned s_best[kPairWaves][64];
+    const unsigned l = threadIdx.x & 63u, part = l / kOwn;
+    const unsigned w = (unsigned)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const unsigned i = blockIdx.x * kOwn + l % kOwn;
+    const int2* __restrict__ pos = reinterpret_cast<const int2*>(A.pos);
+    // past the end the last agent of all, whose repeats change no minimum
+    auto load = [&](unsigned j) { return pos[min(j, A.n - 1)]; };
+    const int2 own = load(i);
+    const unsigned pi = pack_pos(own.x, own.y), groups = (A.n + 63) / 64u;
+    unsigned best = kNone;
+    int2 q = load(w * 64u + l);
+    for (unsigned g = w, buf = 0; g < groups; g += kPairWaves, buf ^= 1) {
+        // the wave's LDS writes and reads are in order, and the other buffer
+        // takes the next group, so no barrier is needed
+        reinterpret_cast<unsigned*>(s_pos[w][buf])[l] = pack_pos(q.x, q.y);
+        __builtin_amdgcn_wave_barrier();
+        q = load((g + kPairWaves) * 64u + l);        // in flight meanwhile
+        if (g == blockIdx.x * kOwn / 64u || g * 64u + 64u > A.n) {
+            // its own agents (without the agent itself), or a partial group
+            for (unsigned k = part * kPart; k < part * kPart + kPart; ++k)
+                if (g * 64u + k != i && g * 64u + k < A.n)
+                    best = min(best, dist2(pi, reinterpret_cast<unsigned*>(s_pos[w][buf])[k]));
+            continue;
+        }
+        // four positions per 16-byte LDS read (an agent's lanes read the same
+        // few addresses), so a read serves ten vector instructions
+#pragma unroll
+        for (unsigned k = 0; k < kPart / 4; ++k) {
+            const uint4 v = s_pos[w][buf][part * (kPart / 4) + k];
+            best = min(best, dist2(pi, v.x));
+            best = min(best, dist2(pi, v.y));
+            best = min(best, dist2(pi, v.z));
+            best = min(best, dist2(pi, v.w));
+        }
     }
-    out[i] = d;
+    s_best[w][l] = best;
+    __syncthreads();
+    if (w == 0) {
+#pragma unroll
+        for (int k = 1; k < kPairWaves; ++k) best = min(best, s_best[k][l]);
+#pragma unroll
+        for (unsigned o = kOwn; o < 64; o <<= 1) best = min(best, (unsigned)__shfl_xor((int)best, o));
+        if (l < kOwn && i < A.n)
+            A.out[i] = interaction_of(best, A.d_action[i], A.velocity, A.radius);
+    }
+}
+
+// Nearest neighbour by cells, in two levels so that neither a crowd in a
+// corner of the grid nor empty land slows it: a fixed grid of 64 x 64 blocks of
+// 512 x 512 tiles, and in each block a grid of its own of about as many cells
+// as the block has agents, cells four times as tall as wide.  The agents are
+// sorted block by block, row of cells by row of cells, so any stretch of a row
+// is one contiguous run of sorted agents.
+//   k_near_blocks  agents per block, one row of counts per workgroup; clears
+//                  the cells' counts
+//   k_near_cells   each block's agents, its cells and where they begin
+//   k_near_count   cell of every agent, and its rank in it.  Agents that meet
+//                  another of their workgroup on their very tile are done
+//                  (distance 0), and one of them stands for all, so a crowd on
+//                  one tile makes no long run.
+//   k_near_sum     agents of every stretch of kNearScan cells (many agents)
+//   k_near_scan    first sorted place of every cell
+//   k_near_place   agents into their places
+//   k_near_find    the search, one agent per lane in sorted order, and the
+//                  result
+// Whatever the workspace holds (two calls that share one, against the rules),
+// every index stays inside its array.
+constexpr unsigned kNearThreads = 256;
+constexpr unsigned kNearSide = 64;                    // blocks per side
+constexpr unsigned kNearBlocks = kNearSide * kNearSide;
+constexpr unsigned kNearShift = 9;                    // tiles per block side, log2
+constexpr unsigned kNearTiles = 1u << kNearShift;
+constexpr unsigned kNearRows = 128;                   // most workgroups of k_near_blocks
+constexpr unsigned kNearScan = 4096;                  // cells per workgroup of k_near_scan
+constexpr unsigned kNearSums = 1u << 17;              // agents beyond which k_near_sum runs
+constexpr unsigned kNearShared = 1u << 31;            // the agent shares its tile
+constexpr unsigned kNearFew = 64;                     // agents that a lane simply looks at
+
+struct NearArgs {
+    const int* pos;                   // [n][2]
+    const unsigned* d_action;         // [n] (may be `out`)
+    unsigned* out;                    // [n]
+    unsigned n, velocity, radius;
+    unsigned cells;                   // n, up to a multiple of kNearScan
+    unsigned rows;                    // workgroups of k_near_blocks
+    u64* mask;                        // [kNearSide] block rows' non-empty blocks
+    unsigned* alloc;                  // cells given out
+    uint2* block;                     // [kNearBlocks] first cell; cell shifts (x, y << 4),
+                                      // kNone: no agents
+    unsigned* sum;                    // [cells / kNearScan] agents per stretch, or null
+    unsigned* row;                    // [rows][kNearBlocks]
+    unsigned* count;                  // [cells] agents per cell
+    unsigned* first;                  // [cells + 1] agents before
+    unsigned* cell;                   // [n] agent's cell, kNone: another one stands for it
+    unsigned* rank;                   // [n] its rank in the cell; top bit: it shares its tile
+    unsigned* spos;                   // [n] sorted packed positions
+    unsigned* sid;                    // [n] and their agents; top bit as in rank
+};
+
+__device__ __forceinline__ unsigned near_block_of(unsigned p) {
+    return ((p >> (16 + kNearShift)) & (kNearSide - 1)) * kNearSide +
+           ((p & 0x7FFFu) >> kNearShift);
+}
+
+// Lanes of `mask` below this one.
+__device__ __forceinline__ unsigned lanes_below(u64 mask) {
+    return __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32),
+                                     __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u));
+}
+
+__global__ void __launch_bounds__(1024) k_near_blocks(NearArgs A) {
+    __shared__ unsigned s_cnt[kNearBlocks];
+    const unsigned t = threadIdx.x, step = gridDim.x * 1024u;
+#pragma unroll
+    for (unsigned k = 0; k < kNearBlocks; k += 1024) s_cnt[k + t] = 0;
+    uint4* count = reinterpret_cast<uint4*>(A.count);
+    for (unsigned c = blockIdx.x * 1024u + t; c < A.cells / 4; c += step)
+        count[c] = make_uint4(0, 0, 0, 0);
+    if (blockIdx.x == 0 && t == 0) *A.alloc = 0;
+    __syncthreads();
+    const int2* __restrict__ pos = reinterpret_cast<const int2*>(A.pos);
+    for (u64 i0 = blockIdx.x * 1024u; i0 < A.n; i0 += step) {      // workgroup-uniform
+        const bool valid = i0 + t < A.n;
+        unsigned b = 0;
+        if (valid) {
+            const int2 q = pos[i0 + t];
+            b = near_block_of(pack_pos(q.x, q.y));
+        }
+        // the first lane's block by one addition of all its lanes (a town
+        // may lie in one block), the others one by one
+        const u64 rest = __ballot(valid);
+        const unsigned b0 = (unsigned)__builtin_amdgcn_readfirstlane((int)b);
+        const u64 m = __ballot(valid && b == b0);
+        if (m && __lane_id() == (unsigned)__builtin_ctzll(m))
+            atomicAdd(&s_cnt[b0], (unsigned)__popcll(m));
+        if (((rest & ~m) >> __lane_id()) & 1) atomicAdd(&s_cnt[b], 1u);
+    }
+    __syncthreads();
+#pragma unroll
+    for (unsigned k = 0; k < kNearBlocks; k += 1024)
+        A.row[(u64)blockIdx.x * kNearBlocks + k + t] = s_cnt[k + t];
+}
+
+// A row of blocks per workgroup: its waves add up the rows of counts, then its
+// first wave gives every block 2^floor(log2 agents) cells, reserved for the
+// whole row with one atomic (the order of the block rows does not matter).
+__global__ void __launch_bounds__(1024) k_near_cells(NearArgs A) {
+    __shared__ unsigned s_sum[16][64];
+    const unsigned l = threadIdx.x & 63u, w = threadIdx.x >> 6;
+    const unsigned b = blockIdx.x * 64u + l;
+    unsigned m = 0;
+#pragma unroll 4
+    for (unsigned r = w; r < A.rows; r += 16) m += A.row[(u64)r * kNearBlocks + b];
+    s_sum[w][l] = m;
+    __syncthreads();
+    if (w) return;
+    m = 0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) m += s_sum[k][l];
+    const u64 some = __ballot(m != 0);               // a workgroup is a block row
+    if (l == 0) A.mask[blockIdx.x] = some;
+    const unsigned lg = m ? 31u - (unsigned)__builtin_clz(m) : 0u;
+    // 2^(2 kNearShift - area) cells of 2^sx x 2^sy tiles, sx + sy = area
+    const unsigned area = 2 * kNearShift - min(lg, 2 * kNearShift);
+    const unsigned sy = min(kNearShift, area - (area > 1 ? (area - 1) / 2 : 0u));
+    const unsigned sx = area - sy;
+    const unsigned cells = m ? 1u << (2 * kNearShift - area) : 0u;
+    unsigned incl = cells;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const unsigned c = __shfl_up(incl, o);
+        if (l >= (unsigned)o) incl += c;
+    }
+    unsigned base = 0;
+    if (l == 63) base = atomicAdd(A.alloc, incl);
+    A.block[b] = make_uint2(__shfl(base, 63) + incl - cells, m ? sx | (sy << 4) : kNone);
+}
+
+// The grid of one block: cell (cx, cy) is cell `base + (cy << sh) + cx` and
+// covers 2^sx x 2^sy tiles.
+struct NearGrid {
+    unsigned base, sx, sy, sh;
+    bool any;
+    __device__ explicit NearGrid(uint2 v)
+        : base(v.x), sx(min(v.y & 15u, kNearShift)), sy(min((v.y >> 4) & 15u, kNearShift)),
+          sh(kNearShift - sx), any(v.y != kNone) {}
+    __device__ unsigned cell(unsigned cx, unsigned cy) const { return base + (cy << sh) + cx; }
+};
+
+__global__ void __launch_bounds__(kNearThreads) k_near_count(NearArgs A) {
+    constexpr unsigned kSlots = 2 * kNearThreads;
+    static_assert(kSlots == 512, "9 hash bits");
+    __shared__ unsigned s_key[kSlots], s_cnt[kSlots];    // tiles of the workgroup's agents
+    const unsigned t = threadIdx.x;
+#pragma unroll
+    for (unsigned k = 0; k < kSlots; k += kNearThreads) {
+        s_key[k + t] = kNone;
+        s_cnt[k + t] = 0;
+    }
+    const u64 i = (u64)blockIdx.x * kNearThreads + t;
+    const bool valid = i < A.n;
+    unsigned c = 0, p = 0, slot = 0, r = 0;
+    if (valid) {
+        const int2 q = reinterpret_cast<const int2*>(A.pos)[i];
+        p = pack_pos(q.x, q.y);
+        const NearGrid g(A.block[near_block_of(p)]);
+        c = min(g.cell((p & (kNearTiles - 1)) >> g.sx, ((p >> 16) & (kNearTiles - 1)) >> g.sy),
+                A.cells - 1);
+        slot = (p * 2654435761u) >> 23;              // multiplicative hash to 9 bits
+    }
+    __syncthreads();
+    if (valid) {
+        for (;;) {                                   // more slots than agents: ends
+            unsigned key = s_key[slot];
+            if (key == kNone) key = atomicCAS(&s_key[slot], kNone, p);
+            if (key == kNone || key == p) break;
+            slot = (slot + 1) & (kSlots - 1);
+        }
+        r = atomicAdd(&s_cnt[slot], 1u);
+    }
+    __syncthreads();
+    if (!valid) return;
+    const bool shared = s_cnt[slot] > 1;
+    if (r == 0) r = atomicAdd(&A.count[c], 1u) | (shared ? kNearShared : 0u);
+    else c = kNone;
+    A.cell[i] = c;
+    A.rank[i] = r;
+    if (shared) A.out[i] = interaction_of(0, A.d_action[i], A.velocity, A.radius);
+}
+
+__global__ void __launch_bounds__(1024) k_near_sum(NearArgs A) {
+    __shared__ unsigned s_sum;
+    if (threadIdx.x == 0) s_sum = 0;
+    __syncthreads();
+    const uint4 v = reinterpret_cast<const uint4*>(A.count)[blockIdx.x * (kNearScan / 4) + threadIdx.x];
+    unsigned all = v.x + v.y + v.z + v.w;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) all += __shfl_xor(all, o);
+    if (__lane_id() == 0) atomicAdd(&s_sum, all);
+    __syncthreads();
+    if (threadIdx.x == 0) A.sum[blockIdx.x] = s_sum;
+}
+
+// Exclusive scan of the counts, kNearScan cells a workgroup, which adds up the
+// cells before its own itself, so no workgroup waits for another: from the
+// sums where there are many (n above kNearSums), else from the counts (at most
+// 1 MiB, which costs less than the launch of k_near_sum).
+__global__ void __launch_bounds__(1024) k_near_scan(NearArgs A) {
+    __shared__ unsigned s_sum[17];
+    const unsigned t = threadIdx.x, l = __lane_id(), w = t >> 6;
+    const unsigned c = blockIdx.x * kNearScan + 4 * t;
+    const uint4* cnt = reinterpret_cast<const uint4*>(A.count);
+    unsigned before = 0;
+    if (A.sum) {
+        for (unsigned q = t; q < blockIdx.x; q += 1024) before += A.sum[q];
+    } else {
+#pragma unroll 4
+        for (unsigned q = t; q < blockIdx.x * (kNearScan / 4); q += 1024) {
+            const uint4 v = cnt[q];
+            before += v.x + v.y + v.z + v.w;
+        }
+    }
+    const uint4 v = cnt[c / 4];
+    const unsigned own = v.x + v.y + v.z + v.w;
+    unsigned incl = own;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const unsigned a = __shfl_up(incl, o);
+        if (l >= (unsigned)o) incl += a;
+        before += __shfl_xor(before, o);
+    }
+    if (t == 0) s_sum[16] = 0;
+    if (l == 63) s_sum[w] = incl;
+    __syncthreads();
+    if (l == 0 && before) atomicAdd(&s_sum[16], before);
+    unsigned ex = incl - own;
+    for (unsigned k = 0; k < w; ++k) ex += s_sum[k];
+    __syncthreads();
+    ex += s_sum[16];
+    *reinterpret_cast<uint4*>(A.first + c) =
+        make_uint4(ex, ex + v.x, ex + v.x + v.y, ex + v.x + v.y + v.z);
+    if (c + 4 == A.cells) A.first[A.cells] = ex + own;
+}
+
+__global__ void __launch_bounds__(kNearThreads) k_near_place(NearArgs A) {
+    const u64 i = (u64)blockIdx.x * kNearThreads + threadIdx.x;
+    if (i >= A.n) return;
+    const unsigned c = A.cell[i], r = A.rank[i];
+    if (c >= A.cells) return;
+    const int2 q = reinterpret_cast<const int2*>(A.pos)[i];
+    const unsigned at = A.first[c] + (r & ~kNearShared);
+    if (at >= A.n) return;
+    A.spos[at] = pack_pos(q.x, q.y);
+    A.sid[at] = (unsigned)i | (r & kNearShared);
+}
+
+// Whole tiles that cover every point nearer than squared distance d2 >= 1:
+// the root of d2 - 1, rounded down; the addend is more than the float's error
+// (0.004 tiles at 2^31), so the result is never too small.
+__device__ __forceinline__ unsigned near_reach(unsigned d2) {
+    return (unsigned)(__builtin_sqrtf((float)(d2 - 1)) + 0.01f);
+}
+
+// Tiles between v and the stretch [lo, hi] (0 inside).
+__device__ __forceinline__ unsigned near_gap(unsigned v, unsigned lo, unsigned hi) {
+    return v < lo ? lo - v : v > hi ? v - hi : 0u;
+}
+
+// One lane's search for the agent nearest to agent k (sorted) at (x, y).
+struct NearSearch {
+    const NearArgs& A;
+    const u64* mask;                  // LDS: block rows' non-empty blocks
+    unsigned k, p, x, y, best;
+
+    __device__ unsigned first(unsigned c) const { return min(A.first[min(c, A.cells)], A.n); }
+
+    __device__ void one(unsigned j) {
+        const unsigned d = dist2(p, A.spos[j]);
+        if (j != k) best = min(best, d);
+    }
+
+    // the sorted agents [lo, hi), which do not hold agent k: sixteen at a time
+    // by four reads, then the rest four at a time (the last one again where
+    // there are fewer)
+    __device__ void part(unsigned lo, unsigned hi) {
+        const unsigned* s = A.spos + lo;
+        unsigned left = hi - min(lo, hi);
+        for (; left >= 16 && best; left -= 16, s += 16) {
+            uint4 q[4];
+            __builtin_memcpy(q, s, sizeof q);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                best = min(best, dist2(p, q[u].x));
+                best = min(best, dist2(p, q[u].y));
+                best = min(best, dist2(p, q[u].z));
+                best = min(best, dist2(p, q[u].w));
+            }
+        }
+        for (unsigned v = 0; v < left && best; v += 4) {
+            unsigned q[4];
+#pragma unroll
+            for (unsigned u = 0; u < 4; ++u) q[u] = s[min(v + u, left - 1)];
+#pragma unroll
+            for (unsigned u = 0; u < 4; ++u) best = min(best, dist2(p, q[u]));
+        }
+    }
+    // the sorted agents [lo, hi)
+    __device__ void run(unsigned lo, unsigned hi) {
+        if (k >= lo && k < hi) {
+            part(lo, k);
+            part(k + 1, hi);
+        } else {
+            part(lo, hi);
+        }
+    }
+
+    // The run of row c of a block at bx, as wide as an agent `gap` tiles off
+    // the row can be nearer than `best`: false if that leaves the block.
+    __device__ bool row(const NearGrid& g, unsigned bx, unsigned c, unsigned gap, unsigned& lo,
+                        unsigned& hi) const {
+        const unsigned w = near_reach(best - gap * gap);
+        if (x + w < bx || x > bx + kNearTiles - 1 + w) return false;
+        const unsigned l = max(x > w ? x - w : 0u, bx) - bx;
+        const unsigned r = min(x + w, bx + kNearTiles - 1) - bx;
+        lo = first(g.cell(l >> g.sx, c));
+        hi = first(g.cell(r >> g.sx, c) + 1);
+        return lo < hi;
+    }
+
+    // Block (qx, qy): its rows from the one nearest outwards, 2 kAhead rows
+    // looked up together, while they are nearer than the best so far.  In long
+    // runs the agents about x come first, which mostly shortens them.
+    __device__ void block(unsigned qx, unsigned qy) {
+        constexpr int kAhead = 4;
+        const NearGrid g(A.block[qy * kNearSide + qx]);
+        if (!g.any) return;
+        const unsigned bx = qx << kNearShift, by = qy << kNearShift;
+        const unsigned rows = kNearTiles >> g.sy;
+        const unsigned near = (min(max(y, by), by + kNearTiles - 1) - by) >> g.sy;
+        const unsigned cx = (min(max(x, bx), bx + kNearTiles - 1) - bx) >> g.sx;
+        // from above or below, the empty rows before the first agent are passed
+        // over: the agents of whole rows are a difference of two cells' places
+        unsigned start = 0;
+        if (y < by || y > by + kNearTiles - 1) {
+            const bool below = y > by + kNearTiles - 1;      // of the block
+            const unsigned edge = first(g.cell(0, below ? rows : 0));
+            unsigned over = rows - 1;                        // the row sought is in [start, over]
+            while (start < over) {
+                const unsigned mid = (start + over) / 2;
+                if (first(g.cell(0, below ? rows - 1 - mid : mid + 1)) != edge) over = mid;
+                else start = mid + 1;
+            }
+        }
+        for (unsigned d0 = start; d0 < rows; d0 += kAhead) {
+            unsigned lo[2 * kAhead], hi[2 * kAhead];
+            auto place = [&](int s, unsigned& c, unsigned& gap) {
+                const unsigned d = d0 + (s >> 1);
+                c = s & 1 ? near + d : near - d;
+                if (s & 1 ? d == 0 || c >= rows : d > near) return false;
+                gap = near_gap(y, by + (c << g.sy), by + ((c + 1) << g.sy) - 1);
+                return gap * gap < best;
+            };
+            bool any = false, wide = false;
+#pragma unroll
+            for (int s = 0; s < 2 * kAhead; ++s) {
+                unsigned c, gap;
+                lo[s] = hi[s] = 0;
+                if (!place(s, c, gap)) continue;
+                any = true;
+                if (!row(g, bx, c, gap, lo[s], hi[s])) lo[s] = hi[s] = 0;
+                wide |= hi[s] - lo[s] > 32;
+            }
+            if (!any) break;
+            if (wide) {
+                unsigned j[2 * kAhead];
+#pragma unroll
+                for (int s = 0; s < 2 * kAhead; ++s) {
+                    unsigned c, gap;
+                    j[s] = hi[s] > lo[s] && place(s, c, gap) ? first(g.cell(cx, c)) : 0u;
+                }
+#pragma unroll
+                for (int s = 0; s < 2 * kAhead; ++s) {
+                    if (j[s] >= lo[s] && j[s] < hi[s]) one(j[s]);
+                    if (j[s] > lo[s] && j[s] <= hi[s]) one(j[s] - 1);
+                }
+#pragma unroll
+                for (int s = 0; s < 2 * kAhead; ++s) {
+                    unsigned c, gap;
+                    if (hi[s] - lo[s] <= 32) continue;
+                    if (!place(s, c, gap) || !row(g, bx, c, gap, lo[s], hi[s])) lo[s] = hi[s] = 0;
+                }
+            }
+            // few agents: eight at a time whatever their row; else row by row
+            unsigned end[2 * kAhead], total = 0;
+#pragma unroll
+            for (int s = 0; s < 2 * kAhead; ++s) end[s] = total += hi[s] - lo[s];
+            if (total <= kNearFew) {
+                for (unsigned v = 0; v < total && best; v += 8) {
+                    unsigned q[8], at[8];
+#pragma unroll
+                    for (unsigned u = 0; u < 8; ++u) {
+                        const unsigned w = min(v + u, total - 1);
+                        at[u] = lo[0] + w;
+#pragma unroll
+                        for (int s = 1; s < 2 * kAhead; ++s)
+                            at[u] = w >= end[s - 1] ? lo[s] + (w - end[s - 1]) : at[u];
+                        q[u] = A.spos[at[u]];
+                    }
+#pragma unroll
+                    for (unsigned u = 0; u < 8; ++u) {
+                        const unsigned d = dist2(p, q[u]);
+                        if (at[u] != k) best = min(best, d);
+                    }
+                }
+                continue;
+            }
+            for (int s = 0; s < 2 * kAhead; ++s) {   // one copy of the run's code
+                unsigned l = 0, h = 0;
+#pragma unroll
+                for (int q = 0; q < 2 * kAhead; ++q) {
+                    l = q == s ? lo[q] : l;
+                    h = q == s ? hi[q] : h;
+                }
+                if (l < h) run(l, h);
+            }
+        }
+    }
+
+    // `best` to one more than a distance within which some other agent must
+    // be: the farthest corner of a non-empty block, from the nearest blocks of
+    // each block row outwards.  `alone`: the agent is its block's only one.
+    __device__ void bound(bool alone) {
+        const unsigned qx = x >> kNearShift, qy = y >> kNearShift;
+        auto take = [&](unsigned bx, unsigned by) {
+            const unsigned x0 = bx << kNearShift, y0 = by << kNearShift;
+            const unsigned dx = max(x > x0 ? x - x0 : x0 - x, near_far(x, x0));
+            const unsigned dy = max(y > y0 ? y - y0 : y0 - y, near_far(y, y0));
+            best = min(best, dx * dx + dy * dy + 1);
+        };
+        for (unsigned d = 0; d < kNearSide; ++d) {
+            const unsigned gap = d ? min(y - ((qy - d + 1) << kNearShift) + 1,
+                                         ((qy + d) << kNearShift) - y) : 0u;
+            if (gap < 46341u && gap * gap >= best) break;
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                if (s == 0 ? d > qy : d == 0 || qy + d >= kNearSide) continue;
+                const unsigned r = s == 0 ? qy - d : qy + d;
+                u64 m = mask[r];
+                if (d == 0 && alone) m &= ~(1ull << qx);
+                const u64 left = m & ((2ull << qx) - 1), right = m & ~((2ull << qx) - 1);
+                if (left) take(63u - (unsigned)__builtin_clzll(left), r);
+                if (right) take((unsigned)__builtin_ctzll(right), r);
+            }
+        }
+    }
+    __device__ static unsigned near_far(unsigned v, unsigned lo) {
+        const unsigned hi = lo + kNearTiles - 1;
+        return v > hi ? v - hi : hi - v;
+    }
+
+    // every block but its own that may hold a nearer agent
+    __device__ void others() {
+        const unsigned qx = x >> kNearShift, qy = y >> kNearShift;
+        for (unsigned d = 0; d < kNearSide; ++d) {
+            bool any = false;
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                if (s == 0 ? d > qy : d == 0 || qy + d >= kNearSide) continue;
+                const unsigned r = s == 0 ? qy - d : qy + d, by = r << kNearShift;
+                const unsigned gy = near_gap(y, by, by + kNearTiles - 1);
+                if (gy * gy >= best) continue;
+                any = true;
+                const unsigned w = near_reach(best);
+                const unsigned b0 = (x > w ? x - w : 0u) >> kNearShift;
+                const unsigned b1 = min(x + w, 0x7FFFu) >> kNearShift;
+                u64 m = mask[r] & (~0ull << b0) & (~0ull >> (63 - b1));
+                if (d == 0) m &= ~(1ull << qx);
+                for (; m; m &= m - 1) {
+                    const unsigned b = (unsigned)__builtin_ctzll(m), bx = b << kNearShift;
+                    const unsigned gx = near_gap(x, bx, bx + kNearTiles - 1);
+                    if (gx * gx + gy * gy < best) block(b, r);
+                }
+            }
+            if (!any) break;
+        }
+    }
+};
+
+__global__ void __launch_bounds__(kNearThreads) k_near_find(NearArgs A) {
+    __shared__ u64 s_mask[kNearSide];
+    if (threadIdx.x < kNearSide) s_mask[threadIdx.x] = A.mask[threadIdx.x];
+    __syncthreads();
+    const u64 k64 = (u64)blockIdx.x * kNearThreads + threadIdx.x;
+    const unsigned n = min(A.first[A.cells], A.n);   // sorted agents
+    if (k64 >= n) return;
+    const unsigned k = (unsigned)k64, id = A.sid[k], p = A.spos[k] & 0x7FFF7FFFu, x = p & 0xFFFFu, y = p >> 16;
+    if (id & kNearShared) return;                    // done by k_near_count
+    NearSearch S{A, s_mask, k, p, x, y, kNone};
+
+    // Its cell, three cells either side and the rows above and below it, as
+    // far as the block goes: their runs are looked up together, and in even
+    // country that is the whole search.
+    const unsigned qx = x >> kNearShift, qy = y >> kNearShift;
+    const NearGrid g(A.block[qy * kNearSide + qx]);
+    const unsigned bx = qx << kNearShift, by = qy << kNearShift;
+    const unsigned cx = (x - bx) >> g.sx, cy = (y - by) >> g.sy;
+    const unsigned l = cx > 3 ? cx - 3 : 0u, r = min(cx + 3, (kNearTiles >> g.sx) - 1);
+    const unsigned u = cy ? cy - 1 : 0u, d = min(cy + 1, (kNearTiles >> g.sy) - 1);
+    unsigned lo[3], hi[3];
+    lo[0] = S.first(g.cell(l, cy));
+    hi[0] = S.first(g.cell(r, cy) + 1);
+    lo[1] = S.first(g.cell(l, u));
+    hi[1] = u < cy ? S.first(g.cell(r, u) + 1) : 0u;
+    lo[2] = S.first(g.cell(l, d));
+    hi[2] = d > cy ? S.first(g.cell(r, d) + 1) : 0u;
+    const unsigned s0 = S.first(g.cell(cx, cy)), e0 = S.first(g.cell(cx, cy) + 1);
+    const unsigned n0 = hi[0] - min(lo[0], hi[0]), n1 = hi[1] - min(lo[1], hi[1]);
+    const unsigned total = n0 + n1 + (hi[2] - min(lo[2], hi[2]));
+    // squared distances below which any agent of the block, and any agent at
+    // all, was looked at here
+    unsigned here, all;
+    if (total <= kNearFew) {
+        for (unsigned v = 0; v < total; v += 8) {
+            unsigned j[8], q[8];
+#pragma unroll
+            for (unsigned u8 = 0; u8 < 8; ++u8) {
+                const unsigned w = min(v + u8, total - 1);
+                j[u8] = w < n0 ? lo[0] + w : w - n0 < n1 ? lo[1] + (w - n0) : lo[2] + (w - n0 - n1);
+                q[u8] = A.spos[j[u8]];
+            }
+#pragma unroll
+            for (unsigned u8 = 0; u8 < 8; ++u8) {
+                const unsigned d2 = dist2(p, q[u8]);
+                if (j[u8] != k) S.best = min(S.best, d2);
+            }
+        }
+        constexpr unsigned kOpen = 1u << 15;         // the block's own edge
+        const unsigned ex = min(l ? x - bx - (l << g.sx) + 1 : kOpen,
+                                r + 1 < kNearTiles >> g.sx ? bx + ((r + 1) << g.sx) - x : kOpen);
+        const unsigned ey = min(u ? y - by - (u << g.sy) + 1 : kOpen,
+                                d + 1 < kNearTiles >> g.sy ? by + ((d + 1) << g.sy) - y : kOpen);
+        const unsigned e = min(ex, ey);
+        const unsigned f = min(min(x - bx, bx + kNearTiles - 1 - x),
+                               min(y - by, by + kNearTiles - 1 - y)) + 1;
+        here = e * e;
+        all = min(here, f * f);
+    } else {
+        S.run(s0, e0);
+        here = all = 1;                              // its own tile at least
+    }
+    if (S.best > all) {
+        if (S.best > here) {
+            // the sorted neighbours are mostly near, however empty the cells
+            if (k > 0) S.one(k - 1);
+            if (k + 1 < n) S.one(k + 1);
+            if (near_reach(S.best) > kNearTiles) S.bound(g.sx + g.sy == 2 * kNearShift);
+            S.block(qx, qy);
+        }
+        S.others();
+    }
+    const unsigned i = id;
+    if (i < A.n) A.out[i] = interaction_of(S.best, A.d_action[i], A.velocity, A.radius);
+}
+
+// The search by cells starts where it is at least as fast whatever the agents'
+// places.  Agents uniform on 2048 x 2048 tiles: all pairs 49 us at 24,000, 78 at
+// 28,000 and 221 at 50,000, the search 36, 36 and 40 us.  A dense town and a
+// few agents very far from it, its slowest case seen: 92 us at 25,000 and 96 to
+// 150 us at 50,000.
+constexpr unsigned kNearAgents = 32768;
+
+inline u64 near_cells(unsigned n) { return ((u64)n + kNearScan - 1) / kNearScan * kNearScan; }
+inline unsigned near_rows(unsigned n) { return std::min<u64>(kNearRows, ((u64)n + 1023) / 1024); }
+
+inline u64 near_bytes(unsigned n) {
+    const u64 cells = near_cells(n);
+    return 16 + 8 * (kNearSide + kNearBlocks) +
+           4 * ((cells / kNearScan + 3) / 4 * 4 + (u64)near_rows(n) * kNearBlocks + 2 * cells + 4 +
+                4 * (u64)n);
 }
 
 inline unsigned obj_blocks(unsigned M, unsigned R) {
@@ -780,12 +1367,13 @@ ss_status ss_hop_distances(const uint32_t* row_off, const uint32_t* col, uint32_
     return SS_OK;
 }
 
-uint64_t ss_interaction_distances_workspace(uint32_t n_agents) { return (uint64_t)n_agents * 4; }
+uint64_t ss_interaction_distances_workspace(uint32_t n_agents) {
+    return n_agents >= kNearAgents ? near_bytes(n_agents) : (uint64_t)n_agents * 4;
+}
 
 }  // extern "C"
 
-// Partial minima of ss_interaction_distances_static (4 MiB): one array per
-// device, held from the library's load until the process ends, shared by
+// Workspace of ss_interaction_distances_static (4 MiB): one array per device, held from the library's load until the process ends, shared by
 // every call on that device.  Host code never uses its name as an address:
 // the device address is looked up once per device (scratch_addr) and kept.
 static __device__ __align__(256) unsigned scratch[1u << 20];
@@ -812,31 +1400,74 @@ ss_status interaction_args(const int32_t* pos_xy, const uint32_t* d_action, uint
     return SS_OK;
 }
 
-// The three interaction kernels on `st`, with d2min [n_agents] as the
-// partial minima (cleared by the first kernel).
-ss_status interaction_launch(const int32_t* pos_xy, const uint32_t* d_action, uint32_t n_agents,
-                             uint32_t velocity, uint32_t radius, uint32_t* out, unsigned* d2min,
-                             int dev, hipStream_t st) {
-    int cus = 256;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) cus = 256;
-    const unsigned iblocks = (n_agents + kPairThreads - 1) / kPairThreads;
-    // split the other agents into slices so that about 8 workgroups run per CU
-    const unsigned want = (unsigned)std::max<u64>(1, (u64)cus * 8 / iblocks);
-    const unsigned tiles = (n_agents + kPairTile - 1) / kPairTile;
-    const unsigned slices = std::min(want, tiles);
-    const unsigned slice = (tiles + slices - 1) / slices * kPairTile;
-    const unsigned nslice = (n_agents + slice - 1) / slice;
-    const unsigned b256 = (n_agents + 255) / 256;
-    hipLaunchKernelGGL(k_pair_init, dim3(b256), dim3(256), 0, st, d2min, n_agents);
+// All pairs on `st`: no workspace.
+template <unsigned kOwn>
+void pair_blocks(const PairArgs& A, hipStream_t st) {
+    hipLaunchKernelGGL(k_pair<kOwn>, dim3((A.n + kOwn - 1) / kOwn), dim3(64 * kPairWaves), 0, st, A);
+}
+
+// 16 agents a workgroup up to 12,288 agents, beyond that 32: the more, smaller
+// workgroups leave fewer of the 256 CUs idle (4,000 agents 6.0 against 7.7 us),
+// but each reads all positions again (24,000 agents 52.7 against 49.4 us; 64 a
+// workgroup 73.5 us, as some CUs then get twice the work of others).
+ss_status pair_launch(const PairArgs& A, hipStream_t st) {
+    if (A.n <= 12288) pair_blocks<16>(A, st);
+    else pair_blocks<32>(A, st);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess)
+        return set_err(SS_ERR_HIP, "interaction distance kernel: %s", hipGetErrorString(e));
+    return SS_OK;
+}
+
+// The search by cells on `st`, in a workspace of near_bytes(A.n) bytes.
+ss_status near_launch(const PairArgs& P, void* workspace, hipStream_t st) {
+    NearArgs A{};
+    A.pos = P.pos;
+    A.d_action = P.d_action;
+    A.out = P.out;
+    A.n = P.n;
+    A.velocity = P.velocity;
+    A.radius = P.radius;
+    A.cells = (unsigned)near_cells(A.n);
+    A.rows = near_rows(A.n);
+    const unsigned chunks = A.cells / kNearScan;
+    A.mask = static_cast<u64*>(workspace);
+    A.alloc = reinterpret_cast<unsigned*>(A.mask + kNearSide);
+    A.block = reinterpret_cast<uint2*>(A.alloc + 4);
+    A.sum = reinterpret_cast<unsigned*>(A.block + kNearBlocks);
+    A.row = A.sum + (chunks + 3) / 4 * 4;
+    A.count = A.row + (u64)A.rows * kNearBlocks;
+    A.first = A.count + A.cells;
+    A.cell = A.first + A.cells + 4;
+    A.rank = A.cell + A.n;
+    A.spos = A.rank + A.n;
+    A.sid = A.spos + A.n;
+    const dim3 one(kNearThreads), all((A.n + kNearThreads - 1) / kNearThreads);
+    hipLaunchKernelGGL(k_near_blocks, dim3(A.rows), dim3(1024), 0, st, A);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(k_pair_min, dim3(iblocks, nslice), dim3(kPairThreads), 0, st, pos_xy,
-                           n_agents, slice, d2min);
+        hipLaunchKernelGGL(k_near_cells, dim3(kNearBlocks / 64), dim3(1024), 0, st, A);
         e = hipGetLastError();
     }
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(k_pair_fin, dim3(b256), dim3(256), 0, st, d2min, d_action, n_agents,
-                           velocity, radius, out);
+        hipLaunchKernelGGL(k_near_count, all, one, 0, st, A);
+        e = hipGetLastError();
+    }
+    if (e == hipSuccess && A.n > kNearSums) {
+        hipLaunchKernelGGL(k_near_sum, dim3(chunks), dim3(1024), 0, st, A);
+        e = hipGetLastError();
+    }
+    if (A.n <= kNearSums) A.sum = nullptr;
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(k_near_scan, dim3(chunks), dim3(1024), 0, st, A);
+        e = hipGetLastError();
+    }
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(k_near_place, all, one, 0, st, A);
+        e = hipGetLastError();
+    }
+    if (e == hipSuccess) {
+        hipLaunchKernelGGL(k_near_find, all, one, 0, st, A);
         e = hipGetLastError();
     }
     if (e != hipSuccess)
@@ -878,22 +1509,24 @@ ss_status ss_interaction_distances(const int32_t* pos_xy, const uint32_t* d_acti
     ss_status st = interaction_args(pos_xy, d_action, n_agents, velocity, out, &dev);
     if (st != SS_OK || n_agents == 0) return st;
     if (!workspace) return set_err(SS_ERR_ARG, "NULL argument");
-    const u64 need = ss_interaction_distances_workspace(n_agents);
-    if (workspace_bytes < need)
+    const u64 least = (u64)n_agents * 4, full = ss_interaction_distances_workspace(n_agents);
+    if (workspace_bytes < least)
         return set_err(SS_ERR_ARG, "workspace_bytes %llu < %llu", (unsigned long long)workspace_bytes,
-                       (unsigned long long)need);
-    if (!device_range_ok(workspace, need, dev))
+                       (unsigned long long)least);
+    // a workspace of four bytes an agent takes all pairs
+    const bool near = n_agents >= kNearAgents && workspace_bytes >= full &&
+                      reinterpret_cast<uintptr_t>(workspace) % 16 == 0;
+    if (!device_range_ok(workspace, near ? full : least, dev))
         return set_err(SS_ERR_ARG, "every array must be device memory of the current device (%d)",
                        dev);
-    return interaction_launch(pos_xy, d_action, n_agents, velocity, radius, out,
-                              static_cast<unsigned*>(workspace), dev,
-                              static_cast<hipStream_t>(stream));
+    const PairArgs A{pos_xy, d_action, out, n_agents, velocity, radius};
+    return near ? near_launch(A, workspace, static_cast<hipStream_t>(stream))
+                : pair_launch(A, static_cast<hipStream_t>(stream));
 }
 
 ss_status ss_interaction_distances_static(const int32_t* pos_xy, const uint32_t* d_action,
                                           uint32_t n_agents, uint32_t velocity, uint32_t radius,
                                           uint32_t* out, void* stream) {
-    static_assert(sizeof(scratch) == kStaticPairAgents * sizeof(unsigned), "scratch size");
     if (n_agents > kStaticPairAgents)
         return set_err(SS_ERR_ARG, "n_agents %u exceeds the %u agents of the static scratch "
                                    "(use ss_interaction_distances with a workspace)",
@@ -901,11 +1534,14 @@ ss_status ss_interaction_distances_static(const int32_t* pos_xy, const uint32_t*
     int dev = -1;
     ss_status st = interaction_args(pos_xy, d_action, n_agents, velocity, out, &dev);
     if (st != SS_OK || n_agents == 0) return st;
-    unsigned* d2min = nullptr;
-    st = scratch_addr(dev, &d2min);
+    const PairArgs A{pos_xy, d_action, out, n_agents, velocity, radius};
+    // the search by cells as far as its workspace fits the scratch
+    if (n_agents < kNearAgents || near_bytes(n_agents) > sizeof(scratch))
+        return pair_launch(A, static_cast<hipStream_t>(stream));
+    unsigned* ws = nullptr;
+    st = scratch_addr(dev, &ws);
     if (st != SS_OK) return st;
-    return interaction_launch(pos_xy, d_action, n_agents, velocity, radius, out, d2min, dev,
-                              static_cast<hipStream_t>(stream));
+    return near_launch(A, ws, static_cast<hipStream_t>(stream));
 }
 
 }  // extern "C"
