@@ -237,13 +237,14 @@ ss_status ss_plan_step(ss_pool* pool, const uint32_t* distances, const uint8_t* 
 /* Evict (Section 3.3: eviction writes the victims' memory back to host):
  * packs the written-back victims' units (victim, then logical unit, then
  * plane) into the eviction staging ring with the pack kernel and copies each
- * such victim's bytes to its host copy with hipMemcpyAsync, ring slot by ring
- * slot.  Clean victims (dirty mask) are not copied.  Returns once
+ * such victim's bytes to its host copy, ring slot by ring slot: with
+ * hipMemcpyAsync, or by one kernel per slot where the victims' bytes are few
+ * (1 MiB each on average, host copies device-mapped and 16-byte aligned).  Clean victims (dirty mask) are not copied.  Returns once
  * queued.  SS_ERR_ORDER unless called right after ss_plan_step. */
 ss_status ss_evict_pack(ss_pool* pool, void* stream);
 
 /* Load (Appendix A, Load(memObj, agentIDs, ...)): copies every loaded agent's
- * host copy into the load staging ring with hipMemcpyAsync and scatters it
+ * host copy into the load staging ring (as ss_evict_pack copies) and scatters it
  * into the agent's new units with the unpack kernel on a side stream.  A slot
  * is unpacked only after the eviction has read every unit it overwrites, so
  * the two directions overlap.  `stream` then waits for the whole step.
@@ -522,10 +523,11 @@ const char* ss_last_error(void);
 
 /* Failure injection, for callers that test their handling of SS_ERR_HIP and
  * SS_ERR_POISONED (a failing HIP call cannot otherwise be provoked without
- * harming the device).  Counting from this call, the n-th copy command issued
- * by ss_evict_pack, ss_prefetch_unpack or ss_loader_pump, in any pool or
- * loader of the process, is not issued and fails as a HIP error would: that
- * call returns SS_ERR_HIP and its pool or loader is poisoned.  n = 0 disarms;
+ * harming the device).  Counting from this call, the n-th copy issued by
+ * ss_evict_pack, ss_prefetch_unpack or ss_loader_pump (one per agent and ring
+ * slot, or per loader chunk; a kernel that moves several agents' bytes counts
+ * as that many), in any pool or loader of the process, is not issued and fails
+ * as a HIP error would: that call returns SS_ERR_HIP and its pool or loader is poisoned.  n = 0 disarms;
  * the hook disarms itself once it has fired.  Work queued before the failing
  * copy still runs, so ss_pool_destroy and ss_loader_destroy stay clean. */
 void ss_debug_fail_copy(uint32_t n);

@@ -197,6 +197,16 @@ struct DuplexArgs {
     u64 capacity;                   // U; unit ids outside [0, U) are skipped
 };
 hipError_t launch_duplex(const DuplexArgs& a, hipStream_t st);
+// A staging slot's bytes to or from the pinned host copies (see k_link).
+struct LinkArgs {
+    char* slot;                     // device
+    char* host;                     // device address of the host copies
+    const u64* off;                 // [first + p] byte offset of logical unit p from host
+    u64 first;
+    unsigned words;                 // 16-byte words in the slot
+    unsigned unit_words;            // and per unit
+};
+hipError_t launch_link(const LinkArgs& a, bool out, hipStream_t st);
 hipError_t launch_pack(const CopyArgs& a, hipStream_t st);
 hipError_t launch_unpack(const CopyArgs& a, hipStream_t st);
 hipError_t launch_zero_u32(unsigned* p, u64 n, hipStream_t st);
@@ -208,6 +218,9 @@ ss_status set_err(ss_status st, const char* fmt, ...);       // sets ss_last_err
 // hipMemcpyAsync of the data-movement paths (pool steps, loader chunks); a
 // copy armed to fail by ss_debug_fail_copy returns hipErrorUnknown unissued.
 hipError_t copy_async(void* dst, const void* src, u64 bytes, hipMemcpyKind kind, hipStream_t st);
+// The same check for a kernel that takes the place of n copies: true if one of
+// them is the armed one, and the kernel must not be launched.
+bool copies_fail(u64 n);
 bool device_range_ok(const void* ptr, u64 bytes, int device); // one device allocation
 bool pinned_range_ok(const void* ptr, u64 bytes);             // pinned host memory
 

@@ -26,11 +26,15 @@
 //                piece of at most 32 KiB moved as one burst of 16-byte
 //                non-temporal accesses;
 //   k_duplex     both directions of a small step in one launch, straight
-//                between the pool's units and the pinned host copies.
+//                between the pool's units and the pinned host copies;
+//   k_link       a staging slot to or from the pinned host copies, where the
+//                agents' runs are too short for copy commands.
 //
 // Nothing here is a dense contraction; all work is integer indexing and byte
 // movement, so there is no MFMA.
 #include "ss_internal.h"
+
+#include <algorithm>
 
 namespace ss {
 
@@ -1683,6 +1687,81 @@ hipError_t launch_duplex(const DuplexArgs& a, hipStream_t st) {
     const u64 blocks = positions * a.item_groups;
     if (blocks > 0x7fffffffull) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_duplex, dim3((unsigned)blocks), dim3(kCopyThreads), 0, st, a);
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
+// small runs between a staging slot and the host copies
+// ---------------------------------------------------------------------------
+
+// A slot whose agents' runs are short goes over the host link in one launch
+// instead of one copy command per agent.  A wave moves kLinkWords consecutive
+// 16-byte words of the slot per lane and round; each word finds its unit's
+// place in the host copies by itself, so units of any size fill the waves.  A
+// round's reads are issued before the round before is stored, and its places
+// one round earlier still, so a round takes one round trip.
+// Bound by the link, which few waves in flight fill: 128 KiB out, 512 KiB in.
+// More is slower, because what the other direction's queue has to read over
+// the link before its kernel starts (its packets and signals) waits behind the
+// bytes in flight: with 256 workgroups each way the two kernels ran one after
+// the other.  10 MB each way: 503 us a step so, 361 us with 8 out and 32 in.
+constexpr unsigned kLinkWords = 4;
+constexpr unsigned kLinkThreads = 256;
+constexpr unsigned kLinkBlocksOut = 8, kLinkBlocksIn = 32;
+
+template <bool kOut>
+__global__ void __launch_bounds__(kLinkThreads) k_link(LinkArgs A) {
+    const unsigned wave = blockIdx.x * (kLinkThreads / 64) + (threadIdx.x >> 6);
+    const unsigned step = gridDim.x * kLinkThreads * kLinkWords;
+    const unsigned last = A.words - 1;
+    auto place = [&](u64 i0, u64 (&off)[kLinkWords]) {
+#pragma unroll
+        for (unsigned k = 0; k < kLinkWords; ++k)
+            off[k] = A.off[A.first + (unsigned)min(i0 + k * 64, (u64)last) / A.unit_words];
+    };
+    auto host = [&](unsigned i, u64 off) {
+        return (gv4u*)(A.host + off) + i % A.unit_words;
+    };
+    v4u r[kLinkWords];
+    gv4u* d[kLinkWords];
+    auto load = [&](u64 i0, const u64 (&off)[kLinkWords]) {
+#pragma unroll
+        for (unsigned k = 0; k < kLinkWords; ++k) {
+            const unsigned i = (unsigned)min(i0 + k * 64, (u64)last);
+            gv4u *s = (gv4u*)A.slot + i, *h = host(i, off[k]);
+            d[k] = kOut ? h : s;
+            r[k] = __builtin_nontemporal_load(kOut ? s : h);
+        }
+    };
+    u64 i0 = (u64)wave * 64 * kLinkWords + lane_id();
+    u64 off[kLinkWords];
+    place(i0, off);
+    load(i0, off);
+    place(i0 + step, off);
+    for (; i0 < A.words; i0 += step) {
+        v4u q[kLinkWords];
+        gv4u* e[kLinkWords];
+#pragma unroll
+        for (unsigned k = 0; k < kLinkWords; ++k) {
+            q[k] = r[k];
+            e[k] = d[k];
+        }
+#pragma unroll
+        for (unsigned k = 0; k < kLinkWords; ++k)
+            if (i0 + k * 64 < A.words) __builtin_nontemporal_store(q[k], e[k]);
+        load(i0 + step, off);
+        place(i0 + 2 * step, off);
+    }
+}
+
+hipError_t launch_link(const LinkArgs& a, bool out, hipStream_t st) {
+    if (a.words == 0) return hipSuccess;
+    if (a.unit_words == 0) return hipErrorInvalidValue;
+    const u64 per = (u64)kLinkThreads * kLinkWords;
+    const unsigned blocks =
+        (unsigned)std::min<u64>(out ? kLinkBlocksOut : kLinkBlocksIn, (a.words + per - 1) / per);
+    if (out) hipLaunchKernelGGL(k_link<true>, dim3(blocks), dim3(kLinkThreads), 0, st, a);
+    else hipLaunchKernelGGL(k_link<false>, dim3(blocks), dim3(kLinkThreads), 0, st, a);
     return hipGetLastError();
 }
 

@@ -14,6 +14,11 @@
 // slot.  The next step's plan waits for the previous step's loads, its
 // evictions (packs and device-to-host copies) and its block-table update.
 //
+// Short runs: a direction whose agents move at most kLinkRunBytes each on
+// average goes between its slots and the host copies by one kernel per slot
+// (k_link) in the place of the copies, on the same streams and in the same
+// order.
+//
 // Direct transfers (direct_bytes): a direction whose bytes in the step are at
 // most the pool's limit skips the staging ring and the copy commands; one
 // pack (or unpack) launch reads (or writes) each unit's place in its agent's
@@ -57,6 +62,14 @@ thread_local std::string g_err;
 // the plan's event instead (a plan queued behind long work on the caller's
 // stream then costs no spinning host core).
 constexpr long kPlanPollUs = 2000;
+
+// Mean bytes per agent up to which a step's staged direction moves each slot
+// over the host link by one kernel (k_link) instead of a copy per agent.  Steps
+// with copies / with k_link, the copies on the copy engines: 200 agents of 64
+// KiB 1,352 / 247 us, 50 of 1 MiB 645 / 527, 30 of 2 MiB 735 / 726, 20 of 4 MiB
+// 718 / 765; on a runtime that copies to the host by kernels of its own: 1,045 /
+// 214, 493 / 413, 499 / 480, 592 / 616, but 4 of 2 MiB 155 / 165.
+constexpr u64 kLinkRunBytes = 1u << 20;
 }  // namespace
 
 namespace {
@@ -65,11 +78,16 @@ std::atomic<uint32_t> g_fail_copy{0};
 }  // namespace
 
 namespace ss {
-hipError_t copy_async(void* dst, const void* src, u64 bytes, hipMemcpyKind kind, hipStream_t st) {
-    uint32_t n = g_fail_copy.load(std::memory_order_relaxed);
-    while (n != 0 && !g_fail_copy.compare_exchange_weak(n, n - 1, std::memory_order_relaxed)) {
+bool copies_fail(u64 n) {
+    uint32_t left = g_fail_copy.load(std::memory_order_relaxed);
+    while (left != 0 && !g_fail_copy.compare_exchange_weak(
+                            left, left > n ? (uint32_t)(left - n) : 0u, std::memory_order_relaxed)) {
     }
-    if (n == 1) return hipErrorUnknown;              // this is the armed copy: not issued
+    return left != 0 && left <= n;                   // the armed copy is among them
+}
+
+hipError_t copy_async(void* dst, const void* src, u64 bytes, hipMemcpyKind kind, hipStream_t st) {
+    if (copies_fail(1)) return hipErrorUnknown;      // not issued
     return hipMemcpyAsync(dst, src, bytes, kind, st);
 }
 
@@ -114,7 +132,8 @@ struct ss_pool {
     u64 units_per_slot = 0;
     u64 slot_bytes = 0;
     u64 direct_bytes = 0;          // directions of at most this many bytes go direct
-    char* host_dev = nullptr;      // device address of the host copies (direct mode)
+    char* host_dev = nullptr;      // device address of the host copies, or null
+    bool link_ok = false;          // every host copy is device-mapped and 16-byte aligned
 
     // device metadata
     unsigned* d_units = nullptr;
@@ -132,8 +151,8 @@ struct ss_pool {
     int *d_vunits = nullptr, *d_lunits = nullptr, *d_free_old = nullptr, *d_wunits = nullptr;
     unsigned char* d_vwritten = nullptr;
     u64* d_woff = nullptr;
-    u64* d_host_off = nullptr;     // direct mode: [N] host-copy offsets
-    u64 *d_whost = nullptr, *d_lhost = nullptr;   // direct mode: [U] per moved unit
+    u64* d_host_off = nullptr;     // with host_dev: [N] host-copy offsets
+    u64 *d_whost = nullptr, *d_lhost = nullptr;   // with host_dev: [U] per moved unit
     u64* d_rhost = nullptr;                       // direct mode: [U] per released position
     unsigned* d_wrel = nullptr;                   // direct mode: [U] per written-back position
     PlanResult* d_res = nullptr;
@@ -198,6 +217,7 @@ struct ss_pool {
     PlanResult res{};
     std::vector<u64> voff, loff, woff;
     std::vector<long long> last_written;   // per victim: last written-back victim <= i, or -1
+    unsigned n_written = 0;                // written-back victims
 
     State state = kIdle;
     bool poisoned = false;
@@ -458,11 +478,31 @@ void host_offsets(ss_pool* p) {
     p->woff.resize(r.n_victims + 1);
     p->last_written.resize(r.n_victims);
     p->woff[0] = 0;
+    p->n_written = 0;
     for (unsigned i = 0; i < r.n_victims; ++i) {
         const bool w = p->h_vwritten[i] != 0;
+        p->n_written += w;
         p->woff[i + 1] = p->woff[i] + (w ? p->s[p->h_victims[i]] : 0);
         p->last_written[i] = w ? (long long)i : (i ? p->last_written[i - 1] : -1);
     }
+}
+
+// Whether a staged direction of `units` units of `agents` agents moves its
+// slots by k_link: their runs are short, and every slot's words count in 32 bits.
+bool by_link(const ss_pool* p, u64 units, u64 agents) {
+    return p->link_ok && units * p->unit_bytes <= agents * kLinkRunBytes &&
+           p->slot_bytes / 16 < (1ull << 31);
+}
+
+LinkArgs link_args(const ss_pool* p, char* slot, const u64* off, u64 first, u64 units) {
+    LinkArgs A{};
+    A.slot = slot;
+    A.host = p->host_dev;
+    A.off = off;
+    A.first = first;
+    A.words = (unsigned)(units * p->unit_bytes / 16);
+    A.unit_words = (unsigned)(p->unit_bytes / 16);
+    return A;
 }
 
 ss_status check_usable(ss_pool* p) {
@@ -682,21 +722,28 @@ ss_status ss_pool_create(const ss_pool_desc* d, ss_pool** out) {
     CREATE_TRY(dalloc(&p->d_lunits, U));
     CREATE_TRY(dalloc(&p->d_free_old, U));
     CREATE_TRY(dalloc(&p->d_wunits, U));
-    if (p->direct_bytes) {
-        if (hipHostGetDevicePointer(reinterpret_cast<void**>(&p->host_dev), p->host, 0) !=
-            hipSuccess) {
-            (void)hipGetLastError();
+    if (hipHostGetDevicePointer(reinterpret_cast<void**>(&p->host_dev), p->host, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        p->host_dev = nullptr;
+        if (p->direct_bytes) {
             free_pool(p);
             return set_err(SS_ERR_ARG, "direct_bytes > 0 needs host_backing that the device can "
                                        "access (pinned, mapped)");
         }
+    }
+    if (p->host_dev) {
+        // unit_bytes is a multiple of 16, so aligned offsets align every word
+        p->link_ok = reinterpret_cast<uintptr_t>(p->host_dev) % 16 == 0;
+        for (u64 off : p->host_off) p->link_ok = p->link_ok && off % 16 == 0;
         CREATE_TRY(dalloc(&p->d_host_off, N));
         CREATE_TRY(dalloc(&p->d_whost, U));
         CREATE_TRY(dalloc(&p->d_lhost, U));
-        CREATE_TRY(dalloc(&p->d_rhost, U));
-        CREATE_TRY(dalloc(&p->d_wrel, U));
         CREATE_TRY(hipMemcpy(p->d_host_off, p->host_off.data(), N * sizeof(u64),
                              hipMemcpyHostToDevice));
+    }
+    if (p->direct_bytes) {
+        CREATE_TRY(dalloc(&p->d_rhost, U));
+        CREATE_TRY(dalloc(&p->d_wrel, U));
     }
     CREATE_TRY(dalloc(&p->d_vwritten, N));
     CREATE_TRY(dalloc(&p->d_woff, N + 1));
@@ -1088,6 +1135,7 @@ ss_status ss_evict_pack(ss_pool* p, void* stream) {
         if (timing) TRY_HIP(p, hipEventRecord(tp->b, so), true);
         TRY_HIP(p, hipEventRecord(p->ev_packed[0], so), true);
     }
+    const bool link = !direct && by_link(p, total, p->n_written);
     size_t vi = 0;
     for (u64 k = 0; !direct && k < nslots; ++k) {
         const u64 p0 = k * ups, p1 = std::min(total, p0 + ups);
@@ -1111,14 +1159,22 @@ ss_status ss_evict_pack(ss_pool* p, void* stream) {
         }
         // each written-back victim's bytes inside [p0, p1) go to its host copy
         while (vi < p->res.n_victims && p->woff[vi + 1] <= p0) vi++;
+        u64 runs = 0;
         for (size_t i = vi; i < p->res.n_victims && p->woff[i] < p1; ++i) {
             if (p->woff[i + 1] == p->woff[i]) continue;              // clean victim
+            ++runs;
+            if (link) continue;
             const u64 lo = std::max(p0, p->woff[i]), hi = std::min(p1, p->woff[i + 1]);
             const unsigned v = p->h_victims[i];
             char* dst = p->host + p->host_off[v] + (lo - p->woff[i]) * p->unit_bytes;
             const char* src = slot + (lo - p0) * p->unit_bytes;
             TRY_HIP(p, copy_async(dst, src, (hi - lo) * p->unit_bytes, hipMemcpyDeviceToHost,
                                   p->st_out), true);
+        }
+        if (link) {
+            TRY_HIP(p, copies_fail(runs) ? hipErrorUnknown
+                                         : launch_link(link_args(p, slot, p->d_whost, p0, p1 - p0),
+                                                       true, p->st_out), true);
         }
         if (timing) TRY_HIP(p, hipEventRecord(tp->b, p->st_out), true);
     }
@@ -1178,6 +1234,7 @@ ss_status ss_prefetch_unpack(ss_pool* p, void* stream) {
         TRY_HIP(p, launch_unpack(C, si), true);
         if (timing) TRY_HIP(p, hipEventRecord(tp->b, si), true);
     }
+    const bool link = !direct && by_link(p, total, p->res.n_loads);
     size_t li = 0, ri = 0;
     // host-to-device copies of slot k into the ring
     auto issue_h2d = [&](u64 k) -> ss_status {
@@ -1190,13 +1247,21 @@ ss_status ss_prefetch_unpack(ss_pool* p, void* stream) {
             TRY_HIP(p, hipEventRecord(tp->a, p->st_in), true);
         }
         while (li < p->res.n_loads && p->loff[li + 1] <= q0) li++;
+        u64 runs = 0;
         for (size_t i = li; i < p->res.n_loads && p->loff[i] < q1; ++i) {
+            ++runs;
+            if (link) continue;
             const u64 lo = std::max(q0, p->loff[i]), hi = std::min(q1, p->loff[i + 1]);
             const unsigned a = p->h_loads[i];
             const char* src = p->host + p->host_off[a] + (lo - p->loff[i]) * p->unit_bytes;
             char* dst = slot + (lo - q0) * p->unit_bytes;
             TRY_HIP(p, copy_async(dst, src, (hi - lo) * p->unit_bytes, hipMemcpyHostToDevice,
                                   p->st_in), true);
+        }
+        if (link) {
+            TRY_HIP(p, copies_fail(runs) ? hipErrorUnknown
+                                         : launch_link(link_args(p, slot, p->d_lhost, q0, q1 - q0),
+                                                       false, p->st_in), true);
         }
         if (timing) TRY_HIP(p, hipEventRecord(tp->b, p->st_in), true);
         return SS_OK;

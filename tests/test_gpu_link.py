@@ -1,0 +1,108 @@
+"""Short runs over the host link: the kernel that takes the place of per-agent
+copies (k_link) and the loader's unpack straight from the host copy, against the
+oracle at the sizes where they can go wrong."""
+import numpy as np
+import pytest
+
+import workloads as W
+from gpu_harness import fill_host, run_parity
+from paper_2601_21473_amd import binding as B
+from paper_2601_21473_amd.memory import DeviceBuffer, PoolMemory
+
+pytestmark = pytest.mark.gpu
+KIB = 1024
+
+
+def ragged_trace(chunks, n_agents, max_units, seed):
+    rng = np.random.default_rng(seed)
+    units = rng.integers(1, max_units + 1, n_agents).astype(np.uint32)
+    steps, k = 12, max(1, n_agents // 5)
+    active = np.zeros((steps, n_agents), np.uint8)
+    for t in range(steps):
+        active[t, rng.choice(n_agents, k, replace=False)] = 1
+    need = int((active.astype(np.int64) * units).sum(1).max())
+    pool = W.PoolSpec("kv", need + need // 3 + 1, chunks, units)
+    dist = W.exact_distances(active)
+    return W.Trace("ragged", n_agents, steps, [pool], active, dist, dist.copy(), {})
+
+
+@pytest.mark.parametrize("chunks,n_agents,max_units,slot_units,ring", [
+    ([16], 300, 9, 4096, 2),                    # one 16-byte word a unit
+    ([48, 1040, 16], 120, 5, 7, 2),             # words that fill no wave, many slots a step
+    ([48, 1040, 16], 120, 5, 1, 1),             # one unit a slot, one slot
+    ([4 * KIB] * 4, 200, 6, 64, 3),
+    ([32 * KIB + 16], 40, 40, 50, 2),           # units longer than a round, runs over slots
+    ([256 * KIB], 24, 8, 5, 2),                 # mean runs on either side of 1 MiB
+])
+@pytest.mark.parametrize("dirty", [False, True])
+def test_short_runs(chunks, n_agents, max_units, slot_units, ring, dirty):
+    tr = ragged_trace(chunks, n_agents, max_units, len(chunks) * 100 + max_units)
+    mask = None
+    if dirty:                                   # every other agent is written back
+        mask = (np.arange(n_agents) % 2).astype(np.uint8)
+        mask = np.repeat(mask[None, :], tr.n_steps, 0)
+    st = run_parity(tr, theta=6, slot_units=slot_units, ring_slots=ring, dirty=mask,
+                    label=f"short runs {chunks[0]}x{len(chunks)}")
+    assert st["pack_launches"] > 0 and st["unpack_launches"] > 0
+
+
+def test_unaligned_host_copies():
+    """Host copies off the 16-byte grid keep the copies: same pool, same bytes."""
+    tr = ragged_trace([4 * KIB] * 2, 60, 4, 5)
+    spec, got = tr.pools[0], []
+    content = W.Content(spec, seed=3)
+    for shift in (0, 8):
+        mem = PoolMemory(spec, 2 * 2 * 16 * spec.unit_bytes, 2)
+        fill_host(mem, content, spec)
+        args = mem.desc_args()
+        if shift:
+            mem.host_np[shift:] = mem.host_np[:-shift].copy()
+            args["host_off"] = mem.host_off + np.uint64(shift)
+            sizes = spec.agent_units.astype(np.int64) * spec.unit_bytes
+            keep = args["host_off"].astype(np.int64) + sizes <= mem.host.nbytes
+            args["host_off"][~keep] = 8         # the last agent's copy would end 8 bytes late
+        pool = B.Pool(**args)
+        try:
+            for t in range(tr.n_steps):
+                act = tr.active[t].copy()
+                act[-1] = 0
+                dist = np.ascontiguousarray(tr.dist[t])
+                pool.plan_step(dist.ctypes.data, act.ctypes.data, 0)
+                pool.evict_pack()
+                pool.prefetch_unpack()
+                pool.sync()
+            table = pool.block_table_host_all()
+            got.append((table, mem.units_bytes(table[table >= 0])))
+        finally:
+            pool.close()
+            mem.free()
+    assert np.array_equal(got[0][0], got[1][0])
+    assert np.array_equal(got[0][1], got[1][1])
+
+
+@pytest.mark.parametrize("chunks,slot_units", [
+    ([16], 3), ([48, 1040], 5), ([64 * KIB] * 2, 16), ([64 * KIB] * 2, 17)])   # 2 MiB and above
+def test_loader_chunks(chunks, slot_units):
+    rng = np.random.default_rng(slot_units)
+    units = rng.integers(1, 40, 12).astype(np.uint32)
+    total = int(units.sum())
+    spec = W.PoolSpec("kv", total, chunks, units)
+    mem = PoolMemory(spec, 3 * slot_units * spec.unit_bytes, 3)
+    content = W.Content(spec, seed=1)
+    fill_host(mem, content, spec)
+    to = rng.permutation(total).astype(np.int32)
+    d_to = DeviceBuffer(to.nbytes)
+    d_to.upload(to)
+    off = np.concatenate([[0], np.cumsum(units.astype(np.int64))])
+    loader = B.Loader([mem.desc_args()])
+    try:
+        loader.submit([(0, a, 5, d_to.ptr + 4 * int(off[a])) for a in range(len(units))])
+        loader.pump(10_000)
+        loader.sync()
+        a = np.repeat(np.arange(len(units)), units)
+        j = np.concatenate([np.arange(k) for k in units])
+        assert np.array_equal(mem.units_bytes(to), content.units_bytes(a, j))
+    finally:
+        loader.close()
+        d_to.free()
+        mem.free()
