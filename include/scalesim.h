@@ -351,10 +351,11 @@ ss_status ss_probe_object_distances(const uint32_t* obj_off, const uint32_t* obj
  *   workspace  ss_hop_distances_workspace(n_vertices) bytes of device memory,
  *            8-byte aligned, owned by the caller, no initialisation needed.
  * Every array is device memory of the current device, owned by the caller.
- * The search is queued on `stream` (two ordinary launches, then one
- * cooperative launch for the levels); the call returns without waiting.  The 32-bit word at workspace offset 20 is 1 after
- * the search if a grid barrier wait ever exceeded its bound (the hop counts
- * are then incomplete); it stays 0 otherwise.  n_vertices and n_edges must be
+ * The search is queued on `stream` (two ordinary launches; beyond 4,194,304
+ * vertices a cooperative one besides); the call returns without waiting.  The
+ * 32-bit word at workspace offset 20 is 1 after the search if a wait between
+ * levels ever exceeded its bound (the hop counts are then incomplete); it stays
+ * 0 otherwise.  n_vertices and n_edges must be
  * below 2^31; offsets that break the rules above give unspecified hop counts
  * but no access outside the arrays.  SS_ERR_ARG for NULL, too small or
  * non-device arguments, SS_ERR_HIP if the device has no cooperative launch or

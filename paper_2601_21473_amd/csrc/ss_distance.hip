@@ -29,15 +29,15 @@
 // of random gathers.
 //
 // ss_hop_distances (predefined activation paths): multi-source breadth-first
-// hop counts over a CSR graph in one cooperative launch.
-//   k_bfs       level-synchronous, frontier queues in device memory; every
-//               thread takes one frontier vertex and claims its unvisited
-//               out-neighbours eight edges at a time with atomic
-//               compare-and-swap, appending winners to the next queue with one
-//               counter atomic per wave; a grid barrier (atomic arrival
-//               counter and generation word, bounded spin) separates levels,
-//               so the whole search is one launch and needs no host round
-//               trip per level.
+// hop counts over a CSR graph, level by level in one launch.
+//   k_bfs       the workgroups own stretches of vertices; a level sweeps each
+//               stretch's hop counts for the vertices reached last, claims
+//               their unvisited out-neighbours with compare-and-swap, and
+//               counts its stretch done; nothing else passes between
+//               workgroups, so no host round trip, queue or cache flush
+//               separates levels.
+//   k_queue     very large graphs: frontier queues, levels separated by a
+//               grid barrier in a cooperative launch.
 //
 // ss_interaction_distances (interaction-involved simulations): D =
 // min(D_action, floor(max(0, isqrt(d2) - radius) / velocity)) with d2 the
@@ -293,12 +293,230 @@ __global__ void __launch_bounds__(256) k_obj_fix(const ObjCarry* __restrict__ ca
 // Hop counts
 // ---------------------------------------------------------------------------
 
-constexpr int kBfsThreads = 256;
+constexpr int kBfsThreads = 1024;
 constexpr int kBfsEdges = 8;                 // edges claimed per vertex per round
-constexpr int kBfsVerts = 2;                 // frontier vertices per thread per round
-constexpr unsigned kBfsSpin = 1u << 24;      // barrier spin bound (about 0.5 s)
+constexpr int kBfsVerts = 2;                 // frontier vertices per lane per round
+constexpr unsigned kBfsBatch = 8;            // vertices per lane that a sweep reads at once
+constexpr unsigned kBfsSpin = 1u << 22;      // bound of a wait (about 5 s)
 
 struct BfsArgs {
+    const unsigned* row_off;                 // [V + 1]
+    const unsigned* col;                     // [E]
+    const unsigned* src;                     // [n_src]
+    unsigned V, E, n_src, max_hops;
+    unsigned* hops;                          // [V]
+    unsigned* ctl;                           // [kCtlWords] see kCtl*
+    u64* hint;                               // [V / 64 + 1] visited vertices, or null
+    unsigned chunks;                         // chunks per level
+    unsigned span;                           // vertices per chunk, a multiple of kBfsThreads
+};
+constexpr int kCtlTicket = 4;                // chunks given out
+constexpr int kCtlError = 5;                 // 1 if a wait hit its bound
+constexpr int kCtlDone = 8;                  // [kBfsSlots x 2 words] by level: chunks done (low
+                                             // word), those that reached new vertices (high)
+constexpr unsigned kBfsSlots = 8;
+constexpr unsigned kCtlWords = kCtlDone + 2 * kBfsSlots;
+
+// Every vertex unvisited, control words zero.
+__global__ void __launch_bounds__(kBfsThreads) k_bfs_init(BfsArgs A) {
+    const unsigned v = blockIdx.x * kBfsThreads + threadIdx.x;
+    if (v < A.V) A.hops[v] = kNone;
+    if (A.hint && v <= A.V / 64) A.hint[v] = 0;
+    if (blockIdx.x == 0 && threadIdx.x < kCtlWords) A.ctl[threadIdx.x] = 0;
+}
+
+// Chunk c of the vertices at hop `level`: their unvisited out-neighbours get
+// hop level + 1.  Returns whether this lane reached any.
+__device__ __forceinline__ bool bfs_chunk(const BfsArgs& A, unsigned c, unsigned level,
+                                          unsigned* list) {
+    const unsigned lane = __lane_id(), w = threadIdx.x >> 6;
+    constexpr unsigned kWaves = kBfsThreads / 64;
+    const u64 end = min((u64)(c + 1) * A.span, (u64)A.V);
+    bool found = false;
+    for (u64 b = (u64)c * A.span + w * 64u; b < end; b += (u64)kWaves * 64 * kBfsBatch) {
+        // a sweep of kBfsBatch x 64 vertices; those at this level go to the
+        // wave's list
+        unsigned h[kBfsBatch];
+#pragma unroll
+        for (unsigned k = 0; k < kBfsBatch; ++k) {
+            const u64 v = b + (u64)k * kWaves * 64 + lane;
+            h[k] = kNone;
+            if (v < end)
+                h[k] = __hip_atomic_load(&A.hops[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        unsigned n = 0;
+#pragma unroll
+        for (unsigned k = 0; k < kBfsBatch; ++k) {
+            const u64 v0 = b + (u64)k * kWaves * 64;
+            const u64 m = __ballot(h[k] == level);
+            if (A.hint && m && lane == 0)
+                __hip_atomic_fetch_or(&A.hint[v0 / 64], m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (h[k] == level)
+                list[n + __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
+                                                   __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u))] =
+                    (unsigned)v0 + lane;
+            n += (unsigned)__popcll(m);
+        }
+        __builtin_amdgcn_wave_barrier();
+        for (unsigned i0 = 0; i0 < n; i0 += 64 * kBfsVerts) {
+            unsigned e[kBfsVerts], e1[kBfsVerts];
+#pragma unroll
+            for (int f = 0; f < kBfsVerts; ++f) {
+                const unsigned i = i0 + f * 64u + lane;
+                e[f] = e1[f] = 0;
+                if (i < n) {
+                    const unsigned v = list[i];
+                    e[f] = min(A.row_off[v], A.E);
+                    e1[f] = min(A.row_off[v + 1], A.E);
+                }
+            }
+            bool more = false;
+#pragma unroll
+            for (int f = 0; f < kBfsVerts; ++f) more |= e[f] < e1[f];
+            while (__ballot(more)) {
+                unsigned v[kBfsVerts * kBfsEdges];
+                bool claim[kBfsVerts * kBfsEdges];
+#pragma unroll
+                for (int f = 0; f < kBfsVerts; ++f)
+#pragma unroll
+                    for (int k = 0; k < kBfsEdges; ++k)
+                        v[f * kBfsEdges + k] = e[f] + k < e1[f] ? A.col[e[f] + k] : kNone;
+#pragma unroll
+                for (int k = 0; k < kBfsVerts * kBfsEdges; ++k) claim[k] = v[k] < A.V;
+                if (A.hint) {
+                    u64 g[kBfsVerts * kBfsEdges];
+#pragma unroll
+                    for (int k = 0; k < kBfsVerts * kBfsEdges; ++k)
+                        g[k] = claim[k] ? A.hint[v[k] / 64] : 0;
+#pragma unroll
+                    for (int k = 0; k < kBfsVerts * kBfsEdges; ++k)
+                        claim[k] = claim[k] && !((g[k] >> (v[k] & 63)) & 1);
+                }
+#pragma unroll
+                for (int k = 0; k < kBfsVerts * kBfsEdges; ++k)
+                    if (claim[k]) found |= atomicCAS(&A.hops[v[k]], kNone, level + 1) == kNone;
+                more = false;
+#pragma unroll
+                for (int f = 0; f < kBfsVerts; ++f) {
+                    e[f] += kBfsEdges;
+                    more |= e[f] < e1[f];
+                }
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+    return found;
+}
+
+// The levels, in one launch.  Level 0 places the sources (hop 0); level k + 1
+// expands the vertices at hop k.  The vertices are cut into chunks, each owned
+// by the workgroup that drew its ticket; a level may run once all chunks of the
+// level before it are done, which every workgroup reads off that level's
+// counter itself.  Workgroups that wait long for the first level draw the
+// tickets that are left, so the search ends whatever part of the grid is
+// resident, and an ordinary launch does (a cooperative one costs about 20 us
+// more).  What one workgroup learns of another are the hop counts, which are
+// claimed and read by agent-scope atomics alone, and each claim is complete
+// before its chunk counts as done, so no cache is written back or invalidated
+// between levels.  (The hint may be out of date: a vertex that it misses fails
+// its claim.)  A level is a chain of five round trips to memory: counter,
+// hops, row, columns, claims.
+constexpr unsigned kBfsMost = 512;                   // most chunks
+constexpr unsigned kBfsPatience = 64;                // polls before another ticket is drawn
+
+__global__ void __launch_bounds__(kBfsThreads) k_bfs(BfsArgs A) {
+    __shared__ unsigned s_list[kBfsThreads / 64][64 * kBfsBatch];
+    __shared__ unsigned s_own[kBfsMost], s_n, s_state;
+    __shared__ int s_found[2];
+    u64* done = reinterpret_cast<u64*>(A.ctl + kCtlDone);
+    auto draw = [&]() {                              // thread 0: another chunk, if one is left
+        const unsigned t = __hip_atomic_fetch_add(&A.ctl[kCtlTicket], 1u, __ATOMIC_RELAXED,
+                                                  __HIP_MEMORY_SCOPE_AGENT);
+        const bool mine = t < A.chunks && s_n < kBfsMost;
+        if (mine) s_own[s_n++] = t;
+        return mine;
+    };
+    if (threadIdx.x == 0) {
+        s_n = 0;
+        s_found[0] = s_found[1] = 0;
+        draw();
+    }
+    __syncthreads();
+    unsigned from = 0;                               // owned chunks done at this level
+    for (unsigned level = 0; s_n;) {                 // workgroup-uniform
+        bool found = false;
+        const unsigned own = s_n;
+        for (unsigned q = from; q < own; ++q) {
+            const unsigned c = s_own[q];
+            if (level == 0) {
+                for (u64 i = (u64)c * kBfsThreads + threadIdx.x; i < A.n_src;
+                     i += (u64)A.chunks * kBfsThreads) {
+                    const unsigned v = A.src[i];
+                    if (v >= A.V) continue;
+                    __hip_atomic_exchange(&A.hops[v], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    found = true;
+                }
+            } else {
+                found |= bfs_chunk(A, c, level - 1, s_list[threadIdx.x >> 6]);
+            }
+        }
+        if (__ballot(found) && __lane_id() == 0) s_found[level & 1] = 1;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // every claim is complete
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            const bool any = s_found[level & 1];
+            s_found[~level & 1] = 0;
+            u64* slot = &done[level % kBfsSlots];
+            unsigned state = 0;                      // 0: more chunks of this level, 1: next level,
+                                                     // 2: the search is over
+            u64 v;
+            if (A.chunks == 1) {
+                v = 1ull | ((u64)any << 32);
+            } else {
+                v = __hip_atomic_fetch_add(slot, (u64)(own - from) | ((u64)any << 32),
+                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) +
+                    ((u64)(own - from) | ((u64)any << 32));
+                // the slot of four levels on was last read four levels ago
+                if (s_own[0] == 0 && from == 0)
+                    __hip_atomic_store(&done[(level + kBfsSlots / 2) % kBfsSlots], 0ull,
+                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                for (unsigned spin = 0; (unsigned)v < A.chunks; ++spin) {
+                    if (level == 0 && spin % kBfsPatience == kBfsPatience - 1 && draw()) break;
+                    if (spin > kBfsSpin) {
+                        __hip_atomic_store(&A.ctl[kCtlError], 1u, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+                        state = 2;
+                        break;
+                    }
+                    __builtin_amdgcn_s_sleep(4);             // fewer polls in the counter's way
+                    v = __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+            }
+            if ((unsigned)v >= A.chunks) state = (v >> 32) && level < A.max_hops ? 1 : 2;
+            s_state = state;
+            if (A.hint) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        }
+        __syncthreads();
+        if (s_state == 2) return;
+        if (s_state == 1) {
+            ++level;
+            from = 0;
+        } else {
+            from = own;
+        }
+    }
+}
+
+// Graphs of more than kBfsSweep vertices: frontier queues instead of sweeps over
+// all vertices, whose cost per level grows with them (16 M vertices, one at
+// every level: 30.7 us a level by sweeps, 13.3 by queues; 4 M: 10.5 and 13.3).
+constexpr unsigned kBfsSweep = 1u << 22;
+constexpr int kQueueThreads = 256;
+constexpr int kQueueEdges = 8;               // edges claimed per vertex per round
+constexpr int kQueueVerts = 2;               // frontier vertices per thread per round
+constexpr unsigned kQueueSpin = 1u << 24;    // barrier spin bound (about 0.5 s)
+
+struct QueueArgs {
     const unsigned* row_off;                 // [V + 1]
     const unsigned* col;                     // [E]
     const unsigned* src;                     // [n_src]
@@ -308,11 +526,11 @@ struct BfsArgs {
     uint2* q1;
     unsigned* ctl;                           // [8] see kCtl*
 };
-constexpr int kCtlCnt = 0;                   // [0..2] queue lengths, rotating
-constexpr int kCtlBarCount = 3;              // grid barrier arrivals
-constexpr int kCtlBarGen = 4;                // grid barrier generation
-constexpr int kCtlError = 5;                 // 1 if a barrier wait hit its bound
-constexpr int kCtlLevels = 6;                // levels expanded
+constexpr int kQueueCnt = 0;                   // [0..2] queue lengths, rotating
+constexpr int kQueueBarCount = 3;              // grid barrier arrivals
+constexpr int kQueueBarGen = 4;                // grid barrier generation
+constexpr int kQueueError = 5;                 // 1 if a barrier wait hit its bound
+constexpr int kQueueLevels = 6;                // levels expanded
 
 // Grid-wide barrier for a cooperative launch (all workgroups resident).
 // Thread 0 of each workgroup publishes the workgroup's writes with one
@@ -327,22 +545,22 @@ __device__ bool grid_barrier(unsigned* ctl) {
     __syncthreads();
     if (threadIdx.x == 0) {
         int ok = 1;
-        const unsigned gen = __hip_atomic_load(&ctl[kCtlBarGen], __ATOMIC_RELAXED,
+        const unsigned gen = __hip_atomic_load(&ctl[kQueueBarGen], __ATOMIC_RELAXED,
                                                __HIP_MEMORY_SCOPE_AGENT);
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-        const unsigned arrived = __hip_atomic_fetch_add(&ctl[kCtlBarCount], 1u, __ATOMIC_RELAXED,
+        const unsigned arrived = __hip_atomic_fetch_add(&ctl[kQueueBarCount], 1u, __ATOMIC_RELAXED,
                                                         __HIP_MEMORY_SCOPE_AGENT) + 1;
         if (arrived == gridDim.x) {
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "agent");
-            __hip_atomic_store(&ctl[kCtlBarCount], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_fetch_add(&ctl[kCtlBarGen], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&ctl[kQueueBarCount], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_fetch_add(&ctl[kQueueBarGen], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         } else {
             unsigned spin = 0;
-            while (__hip_atomic_load(&ctl[kCtlBarGen], __ATOMIC_RELAXED,
+            while (__hip_atomic_load(&ctl[kQueueBarGen], __ATOMIC_RELAXED,
                                      __HIP_MEMORY_SCOPE_AGENT) == gen) {
-                if (++spin > kBfsSpin) {
+                if (++spin > kQueueSpin) {
                     ok = 0;
-                    __hip_atomic_store(&ctl[kCtlError], 1u, __ATOMIC_RELAXED,
+                    __hip_atomic_store(&ctl[kQueueError], 1u, __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_AGENT);
                     break;
                 }
@@ -363,7 +581,7 @@ __device__ bool grid_barrier(unsigned* ctl) {
 // holds more than the vertex count).  Called by every lane of the wave.
 template <int n>
 __device__ __forceinline__ void wave_append(const bool (&claim)[n], const unsigned (&v)[n],
-                                            const BfsArgs& A, uint2* q, unsigned* cnt) {
+                                            const QueueArgs& A, uint2* q, unsigned* cnt) {
     u64 m[n];
     unsigned total = 0;
 #pragma unroll
@@ -392,54 +610,54 @@ __device__ __forceinline__ void wave_append(const bool (&claim)[n], const unsign
 }
 
 // Every vertex unvisited, counters and barrier words zero.
-__global__ void __launch_bounds__(kBfsThreads) k_bfs_init(BfsArgs A) {
-    const unsigned v = blockIdx.x * kBfsThreads + threadIdx.x;
+__global__ void __launch_bounds__(kQueueThreads) k_queue_init(QueueArgs A) {
+    const unsigned v = blockIdx.x * kQueueThreads + threadIdx.x;
     if (v < A.V) A.hops[v] = kNone;
     if (blockIdx.x == 0 && threadIdx.x < 8) A.ctl[threadIdx.x] = 0;
 }
 
 // Sources: hop 0, each vertex once, into the first queue.
-__global__ void __launch_bounds__(kBfsThreads) k_bfs_src(BfsArgs A) {
-    const unsigned i = blockIdx.x * kBfsThreads + threadIdx.x;
+__global__ void __launch_bounds__(kQueueThreads) k_queue_src(QueueArgs A) {
+    const unsigned i = blockIdx.x * kQueueThreads + threadIdx.x;
     bool claim[1] = {false};
     unsigned v[1] = {kNone};
     if (i < A.n_src) {
         v[0] = A.src[i];
         if (v[0] < A.V) claim[0] = atomicCAS(&A.hops[v[0]], kNone, 0u) == kNone;
     }
-    wave_append(claim, v, A, A.q0, &A.ctl[kCtlCnt + 0]);
+    wave_append(claim, v, A, A.q0, &A.ctl[kQueueCnt + 0]);
 }
 
 // The levels, in one cooperative launch.
-__global__ void __launch_bounds__(kBfsThreads) k_bfs(BfsArgs A) {
+__global__ void __launch_bounds__(kQueueThreads) k_queue(QueueArgs A) {
     const unsigned lane = __lane_id();
-    const unsigned gsz = gridDim.x * kBfsThreads;
-    const unsigned wbase = blockIdx.x * kBfsThreads + (threadIdx.x & ~63u);   // wave's first thread
+    const unsigned gsz = gridDim.x * kQueueThreads;
+    const unsigned wbase = blockIdx.x * kQueueThreads + (threadIdx.x & ~63u);   // wave's first thread
     for (unsigned level = 0;; ++level) {
         // ordered by the kernel start or the barrier's acquire fence; capped
         // at the queue length
-        const unsigned n = min(__hip_atomic_load(&A.ctl[kCtlCnt + level % 3], __ATOMIC_RELAXED,
+        const unsigned n = min(__hip_atomic_load(&A.ctl[kQueueCnt + level % 3], __ATOMIC_RELAXED,
                                                  __HIP_MEMORY_SCOPE_AGENT), A.V);
         if (n == 0 || level >= A.max_hops) break;
         if (blockIdx.x == 0 && threadIdx.x == 0) {
-            __hip_atomic_store(&A.ctl[kCtlCnt + (level + 2) % 3], 0u, __ATOMIC_RELAXED,
+            __hip_atomic_store(&A.ctl[kQueueCnt + (level + 2) % 3], 0u, __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&A.ctl[kCtlLevels], level + 1, __ATOMIC_RELAXED,
+            __hip_atomic_store(&A.ctl[kQueueLevels], level + 1, __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
         }
         const uint2* cur = (level & 1) ? A.q1 : A.q0;
         uint2* nxt = (level & 1) ? A.q0 : A.q1;
-        unsigned* cnt = &A.ctl[kCtlCnt + (level + 1) % 3];
+        unsigned* cnt = &A.ctl[kQueueCnt + (level + 1) % 3];
         // Large frontiers first read a vertex's state and try to claim it only
         // while unvisited (fewer atomics); small ones go straight to the
         // compare-and-swap (one dependent access less per level).
         const bool precheck = n > 32768u;
-        // each lane expands kBfsVerts frontier vertices per round, eight of
+        // each lane expands kQueueVerts frontier vertices per round, eight of
         // their edges at a time, so that many independent loads are in flight
-        for (unsigned b0 = wbase * kBfsVerts; b0 < n; b0 += gsz * kBfsVerts) {
-            unsigned e[kBfsVerts], e1[kBfsVerts];
+        for (unsigned b0 = wbase * kQueueVerts; b0 < n; b0 += gsz * kQueueVerts) {
+            unsigned e[kQueueVerts], e1[kQueueVerts];
 #pragma unroll
-            for (int f = 0; f < kBfsVerts; ++f) {
+            for (int f = 0; f < kQueueVerts; ++f) {
                 const unsigned i = b0 + f * 64u + lane;
                 const uint2 r = i < n ? cur[i] : make_uint2(0u, 0u);
                 e[f] = r.x;
@@ -447,26 +665,26 @@ __global__ void __launch_bounds__(kBfsThreads) k_bfs(BfsArgs A) {
             }
             bool more = false;
 #pragma unroll
-            for (int f = 0; f < kBfsVerts; ++f) more |= e[f] < e1[f];
+            for (int f = 0; f < kQueueVerts; ++f) more |= e[f] < e1[f];
             while (__ballot(more)) {
-                unsigned v[kBfsVerts * kBfsEdges];
-                bool claim[kBfsVerts * kBfsEdges];
+                unsigned v[kQueueVerts * kQueueEdges];
+                bool claim[kQueueVerts * kQueueEdges];
 #pragma unroll
-                for (int f = 0; f < kBfsVerts; ++f)
+                for (int f = 0; f < kQueueVerts; ++f)
 #pragma unroll
-                    for (int k = 0; k < kBfsEdges; ++k)
-                        v[f * kBfsEdges + k] = e[f] + k < e1[f] ? A.col[e[f] + k] : kNone;
+                    for (int k = 0; k < kQueueEdges; ++k)
+                        v[f * kQueueEdges + k] = e[f] + k < e1[f] ? A.col[e[f] + k] : kNone;
 #pragma unroll
-                for (int k = 0; k < kBfsVerts * kBfsEdges; ++k)
+                for (int k = 0; k < kQueueVerts * kQueueEdges; ++k)
                     claim[k] = v[k] < A.V && (!precheck || A.hops[v[k]] == kNone);
 #pragma unroll
-                for (int k = 0; k < kBfsVerts * kBfsEdges; ++k)
+                for (int k = 0; k < kQueueVerts * kQueueEdges; ++k)
                     if (claim[k]) claim[k] = atomicCAS(&A.hops[v[k]], kNone, level + 1) == kNone;
                 wave_append(claim, v, A, nxt, cnt);
                 more = false;
 #pragma unroll
-                for (int f = 0; f < kBfsVerts; ++f) {
-                    e[f] += kBfsEdges;
+                for (int f = 0; f < kQueueVerts; ++f) {
+                    e[f] += kQueueEdges;
                     more |= e[f] < e1[f];
                 }
             }
@@ -1244,6 +1462,43 @@ hipError_t object_launch(const ObjArgs& A, hipStream_t st) {
 
 }  // namespace
 
+namespace {
+
+// The search by frontier queues on `st`.
+ss_status queue_launch(const QueueArgs& args, int dev, hipStream_t st) {
+    QueueArgs A = args;
+    int coop = 0, cus = 0, per_cu = 0;
+    if (hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess ||
+        !coop || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(k_queue),
+                                                     kQueueThreads, 0) != hipSuccess || per_cu < 1) {
+        (void)hipGetLastError();
+        return set_err(SS_ERR_HIP, "cooperative launch is not available on device %d", dev);
+    }
+    // one workgroup per 512 vertices, at most one per CU: every workgroup
+    // pays an L2 write-back and invalidate at each grid barrier, so fewer,
+    // wider workgroups (two vertices per thread per round) are cheaper
+    const u64 want = ((u64)A.V + kQueueThreads * kQueueVerts - 1) / (kQueueThreads * kQueueVerts);
+    const unsigned grid = (unsigned)std::max<u64>(1, std::min<u64>(want, (u64)cus));
+    hipLaunchKernelGGL(k_queue_init, dim3((A.V + kQueueThreads - 1) / kQueueThreads),
+                       dim3(kQueueThreads), 0, st, A);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess && A.n_src) {
+        hipLaunchKernelGGL(k_queue_src, dim3((A.n_src + kQueueThreads - 1) / kQueueThreads),
+                           dim3(kQueueThreads), 0, st, A);
+        e = hipGetLastError();
+    }
+    if (e == hipSuccess) {
+        void* a[] = {&A};
+        e = hipLaunchCooperativeKernel(reinterpret_cast<const void*>(k_queue), dim3(grid),
+                                       dim3(kQueueThreads), a, 0, st);
+    }
+    if (e != hipSuccess) return set_err(SS_ERR_HIP, "hop distance kernels: %s", hipGetErrorString(e));
+    return SS_OK;
+}
+
+}  // namespace
+
 extern "C" {
 
 ss_status ss_object_distances(const uint32_t* obj_off, const uint32_t* obj_agents,
@@ -1322,15 +1577,21 @@ ss_status ss_hop_distances(const uint32_t* row_off, const uint32_t* col, uint32_
         !device_range_ok(hops, (u64)n_vertices * 4, dev) || !device_range_ok(workspace, need, dev))
         return set_err(SS_ERR_ARG, "every array must be device memory of the current device (%d)",
                        dev);
-    int coop = 0, cus = 0, per_cu = 0;
-    if (hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev) != hipSuccess ||
-        !coop || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(k_bfs),
-                                                     kBfsThreads, 0) != hipSuccess || per_cu < 1) {
-        (void)hipGetLastError();
-        return set_err(SS_ERR_HIP, "cooperative launch is not available on device %d", dev);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    char* ws = static_cast<char*>(workspace);
+    if (n_vertices > kBfsSweep) {
+        const u64 qbytes = ((u64)n_vertices * 8 + 255) & ~255ull;
+        return queue_launch({row_off, col, sources, n_vertices, n_edges, n_sources, max_hops, hops,
+                             reinterpret_cast<uint2*>(ws + 64),
+                             reinterpret_cast<uint2*>(ws + 64 + qbytes),
+                             reinterpret_cast<unsigned*>(ws)}, dev, st);
     }
-    BfsArgs A;
+    int cus = 256;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
+        (void)hipGetLastError();
+        cus = 256;
+    }
+    BfsArgs A{};
     A.row_off = row_off;
     A.col = col;
     A.src = sources;
@@ -1339,29 +1600,25 @@ ss_status ss_hop_distances(const uint32_t* row_off, const uint32_t* col, uint32_
     A.n_src = n_sources;
     A.max_hops = max_hops;
     A.hops = hops;
-    char* ws = static_cast<char*>(workspace);
     A.ctl = reinterpret_cast<unsigned*>(ws);
-    const u64 qbytes = ((u64)n_vertices * 8 + 255) & ~255ull;
-    A.q0 = reinterpret_cast<uint2*>(ws + 64);
-    A.q1 = reinterpret_cast<uint2*>(ws + 64 + qbytes);
-    // one workgroup per 512 vertices, at most one per CU: every workgroup
-    // pays an L2 write-back and invalidate at each grid barrier, so fewer,
-    // wider workgroups (two vertices per thread per round) are cheaper
-    const u64 want = ((u64)n_vertices + kBfsThreads * kBfsVerts - 1) / (kBfsThreads * kBfsVerts);
-    const unsigned grid = (unsigned)std::max<u64>(1, std::min<u64>(want, (u64)cus));
-    hipStream_t st = static_cast<hipStream_t>(stream);
+    // claims that fail cost more than the hint's read once a level has many
+    if (n_vertices >= 32768) A.hint = reinterpret_cast<u64*>(ws + 4 * kCtlWords);
+    // chunks of 1,024 vertices, from 96 chunks on of up to 4,096, at most one
+    // per CU: more workgroups expand faster, but all of them add to and poll one
+    // counter per level (200,000 vertices: 196 chunks 97 us, 98 chunks 86 us;
+    // 50,000: 25 chunks 79 us, 49 chunks 64 us; 1 M: 1,024 chunks of a quarter
+    // of the threads 817 us, 256 chunks 212 us)
+    const u64 V = n_vertices;
+    const u64 want = std::min<u64>(std::max((V + 4095) / 4096, std::min<u64>((V + 1023) / 1024, 96)),
+                                   std::min<unsigned>(kBfsMost, std::max(cus, 1)));
+    A.span = (unsigned)(((V + want - 1) / want + kBfsThreads - 1) / kBfsThreads * kBfsThreads);
+    A.chunks = (unsigned)((V + A.span - 1) / A.span);
     hipLaunchKernelGGL(k_bfs_init, dim3((n_vertices + kBfsThreads - 1) / kBfsThreads),
                        dim3(kBfsThreads), 0, st, A);
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess && n_sources) {
-        hipLaunchKernelGGL(k_bfs_src, dim3((n_sources + kBfsThreads - 1) / kBfsThreads),
-                           dim3(kBfsThreads), 0, st, A);
-        e = hipGetLastError();
-    }
     if (e == hipSuccess) {
-        void* args[] = {&A};
-        e = hipLaunchCooperativeKernel(reinterpret_cast<const void*>(k_bfs), dim3(grid),
-                                       dim3(kBfsThreads), args, 0, st);
+        hipLaunchKernelGGL(k_bfs, dim3(A.chunks), dim3(kBfsThreads), 0, st, A);
+        e = hipGetLastError();
     }
     if (e != hipSuccess) return set_err(SS_ERR_HIP, "hop distance kernels: %s", hipGetErrorString(e));
     return SS_OK;

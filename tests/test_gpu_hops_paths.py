@@ -1,0 +1,74 @@
+"""ss_hop_distances at the sizes where its paths change: the edges of the
+stretches of vertices, the first sizes with the visited hint and with larger
+stretches, and the frontier queues of very large graphs."""
+import numpy as np
+import pytest
+
+from oracle.estimators import hop_distances
+from paper_2601_21473_amd import binding as B
+from paper_2601_21473_amd.memory import DeviceBuffer
+
+pytestmark = pytest.mark.gpu
+NEVER = 0xFFFFFFFF
+
+
+def gpu_hops(off, col, src, max_hops=NEVER, calls=2):
+    v, e = len(off) - 1, len(col)
+    bufs = [DeviceBuffer(4 * (v + 1)), DeviceBuffer(max(4, 4 * e)), DeviceBuffer(max(4, 4 * len(src))),
+            DeviceBuffer(4 * v)]
+    wsb = B.hop_distances_workspace(v)
+    ws = DeviceBuffer(wsb)
+    try:
+        for b, a in zip(bufs, (off, col, src)):
+            if len(a):
+                b.upload(np.asarray(a, np.uint32))
+        ws.upload(np.full(min(wsb, 1 << 20), 0x77, np.uint8))
+        out = []
+        for _ in range(calls):                  # the second call finds the first one's workspace
+            B.hop_distances(bufs[0].ptr, bufs[1].ptr, v, e, bufs[2].ptr, len(src), max_hops,
+                            bufs[3].ptr, ws.ptr, wsb)
+            out.append(bufs[3].download(0, 4 * v).view(np.uint32))
+            assert ws.download(20, 4).view(np.uint32)[0] == 0
+        for h in out[1:]:
+            assert np.array_equal(h, out[0])
+        return out[0]
+    finally:
+        for b in bufs + [ws]:
+            b.free()
+
+
+@pytest.mark.parametrize("v", [1, 2, 1023, 1024, 1025, 2049, 32_767, 32_768, 98_304, 98_305])
+@pytest.mark.parametrize("shape", ["random", "hub", "ring"])
+def test_stretches(v, shape):
+    rng = np.random.default_rng(v)
+    if shape == "random":
+        deg = rng.integers(0, 12, v)
+    elif shape == "hub":                        # one vertex with thousands of edges, few others
+        deg = (rng.random(v) < 0.5).astype(np.int64)
+        deg[v // 2] = min(5000, 3 * v)
+    else:
+        deg = np.ones(v, np.int64)
+    off = np.concatenate([[0], np.cumsum(deg)])
+    col = rng.integers(0, v, off[-1]).astype(np.uint32)
+    src = rng.integers(0, v + 2, max(1, v // 200))       # repeated and foreign ids too
+    if shape == "hub":
+        src[0] = v // 2
+    if shape == "ring":
+        step = max(1, v // 60)
+        col = ((np.arange(v) + step) % v).astype(np.uint32)
+        src = np.arange(step)
+    for max_hops in (None, 0, 3):
+        print(f"[hops] v={v} {shape} max_hops={max_hops}", flush=True)
+        got = gpu_hops(off, col, src, NEVER if max_hops is None else max_hops)
+        exp = hop_distances(off, col, src, max_hops)
+        bad = np.flatnonzero(got != exp)
+        assert len(bad) == 0, (bad[:5], got[bad[:5]], exp[bad[:5]])
+
+
+@pytest.mark.parametrize("v", [(1 << 22), (1 << 22) + 1])
+def test_very_large_ring(v):
+    """Closed form: on a ring of step w from its first w vertices, vertex i is
+    i // w hops away."""
+    w = 120_000
+    got = gpu_hops(np.arange(v + 1), (np.arange(v) + w) % v, np.arange(w), calls=1)
+    assert np.array_equal(got, np.arange(v) // w)
