@@ -15,7 +15,7 @@
 // products: every workgroup takes 2048 merge items, whatever the row lengths.
 //   k_obj_prep  merge-path coordinates of every workgroup boundary (16 lanes
 //               per boundary, 16 probes per round) and, in the same launch,
-//               w[a] = 0 if a is active else 2 D[a] + 1, one word per agent.
+//               w[a] = 0 if a is active else D[a] + 1, one word per agent.
 //   k_obj_min   per workgroup: coalesced staging of its row ends and of
 //               w of its references into LDS (the gather of the agents'
 //               words happens here, one load per reference; every thread
@@ -79,7 +79,9 @@ struct ObjArgs {
     unsigned char* out_act;           // [M]
     ObjCarry* carry;                  // [blocks]
     unsigned* coord;                  // [blocks + 1] rows consumed at each block boundary
-    u64* w;                           // [N] 0 if active, else 2 * distance + 1
+    unsigned* w;                      // [N] 0 if active, else distance + 1, at most kNone
+    unsigned* odd;                    // [odd_n] per workgroup that wrote w: it met a distance of
+    unsigned odd_n;                   // kNone - 1, whose w is that of kNone
 };
 
 // Merge-path coordinate (rows consumed) at diagonal d: the first p in
@@ -118,8 +120,12 @@ __device__ unsigned group_path_search(const unsigned* __restrict__ off, unsigned
 // Two independent preparations in one launch.  Blocks [0, part_blocks): the
 // merge-path coordinate of every workgroup boundary b * kObjTile,
 // b = 0..blocks (16 per block).  The rest: w[a] = 0 if agent a is active,
-// else 2 D[a] + 1, so that k_obj_min gathers one word per reference that
-// carries both the distance (w >> 1) and the activity (w == 0).
+// else D[a] + 1, so that k_obj_min gathers one 32-bit word per reference that
+// carries both the distance and the activity.  The two largest distances
+// share a word; in the odd case that the smaller one occurs, k_obj_min reads
+// the distances of those agents again.  (With 64-bit words, which need no such
+// care, the gathers miss the L1 more often and this kernel writes twice as
+// much: 8 M agents and 56 M references 302 us a call, 278 us so.)
 __global__ void __launch_bounds__(256) k_obj_prep(ObjArgs A, unsigned n_bounds,
                                                   unsigned part_blocks) {
     if (blockIdx.x < part_blocks) {
@@ -130,15 +136,37 @@ __global__ void __launch_bounds__(256) k_obj_prep(ObjArgs A, unsigned n_bounds,
         if (valid && (threadIdx.x & 15u) == 0) A.coord[b] = x;
         return;
     }
-    // 2048 agents per block and round, eight per thread, loads before stores
+    // 2048 agents per block and round, eight per thread, loads before stores;
+    // four at a time where the arrays allow it
+    const unsigned blk = blockIdx.x - part_blocks;
     const u64 stride = (u64)(gridDim.x - part_blocks) * 2048u;
-    for (u64 base = (u64)(blockIdx.x - part_blocks) * 2048u + threadIdx.x; base < A.N;
-         base += stride) {
+    bool odd = false;
+    auto word = [&](unsigned d, bool act) {
+        odd |= !act && d == kNone - 1;
+        return act ? 0u : d < kNone - 1 ? d + 1 : kNone;
+    };
+    const bool wide = ((reinterpret_cast<uintptr_t>(A.dist) | reinterpret_cast<uintptr_t>(A.w)) & 15) == 0 &&
+                      (reinterpret_cast<uintptr_t>(A.active) & 3) == 0;
+    for (u64 base = (u64)blk * 2048u; base < A.N; base += stride) {      // workgroup-uniform
+        if (wide && base + 2048 <= A.N) {
+            const u64 q = base / 4 + threadIdx.x;
+            const uint4 d0 = reinterpret_cast<const uint4*>(A.dist)[q];
+            const uint4 d1 = reinterpret_cast<const uint4*>(A.dist)[q + 256];
+            const unsigned a0 = reinterpret_cast<const unsigned*>(A.active)[q];
+            const unsigned a1 = reinterpret_cast<const unsigned*>(A.active)[q + 256];
+            auto four = [&](uint4 d, unsigned a) {
+                return make_uint4(word(d.x, a & 0xFFu), word(d.y, a & 0xFF00u),
+                                  word(d.z, a & 0xFF0000u), word(d.w, a & 0xFF000000u));
+            };
+            reinterpret_cast<uint4*>(A.w)[q] = four(d0, a0);
+            reinterpret_cast<uint4*>(A.w)[q + 256] = four(d1, a1);
+            continue;
+        }
         unsigned dv[8];
         unsigned char ac[8];
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
-            const u64 a = base + k * 256u;
+            const u64 a = base + threadIdx.x + k * 256u;
             dv[k] = 0;
             ac[k] = 0;
             if (a < A.N) {
@@ -148,10 +176,12 @@ __global__ void __launch_bounds__(256) k_obj_prep(ObjArgs A, unsigned n_bounds,
         }
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
-            const u64 a = base + k * 256u;
-            if (a < A.N) A.w[a] = ac[k] ? 0ull : 2ull * dv[k] + 1ull;
+            const u64 a = base + threadIdx.x + k * 256u;
+            if (a < A.N) A.w[a] = word(dv[k], ac[k] != 0);
         }
     }
+    const int any = __syncthreads_or(odd);
+    if (threadIdx.x == 0) A.odd[blk] = any != 0;
 }
 
 // Persistent workgroups: the grid is a multiple of the eight XCDs, and
@@ -173,6 +203,8 @@ __global__ void __launch_bounds__(kObjThreads) k_obj_min(ObjArgs A, unsigned n_t
     constexpr unsigned kXcds = 8;
     const unsigned tid = threadIdx.x;
     const unsigned total = A.M + A.R;
+    unsigned flags = 0;                              // any set: see k_obj_prep
+    for (unsigned k = __lane_id(); k < A.odd_n; k += 64) flags |= A.odd[k];
     const unsigned xcd = blockIdx.x % kXcds, per_xcd = gridDim.x / kXcds;
     const unsigned q = n_tiles / kXcds, rem = n_tiles % kXcds;
     const unsigned t_lo = xcd < rem ? xcd * (q + 1) : rem * (q + 1) + (xcd - rem) * q;
@@ -198,8 +230,9 @@ __global__ void __launch_bounds__(kObjThreads) k_obj_min(ObjArgs A, unsigned n_t
             if (i < nrow) val[k] = min(A.off[o0 + 1 + i], A.R);
             else if (i < nrow + nref) val[k] = A.agents[r0 + (i - nrow)];
         }
-        // one 64-bit word per reference: e = 0 if the agent is active, else 2 D + 1
+        // one word per reference: e = 0 if the agent is active, else D + 1
         unsigned char act[kObjItems];
+        const bool odd = __ballot(flags != 0) != 0;
     #pragma unroll
         for (int k = 0; k < kObjItems; ++k) {
             const unsigned i = tid + k * kObjThreads;
@@ -208,9 +241,9 @@ __global__ void __launch_bounds__(kObjThreads) k_obj_min(ObjArgs A, unsigned n_t
                 const unsigned a = val[k];
                 val[k] = kNone;
                 if (a < A.N) {
-                    const u64 e = A.w[a];
+                    const unsigned e = A.w[a];
                     act[k] = e == 0;
-                    val[k] = (unsigned)(e >> 1);
+                    val[k] = e == 0 ? 0u : e != kNone ? e - 1 : odd ? A.dist[a] : kNone;
                 }
             }
         }
@@ -1373,6 +1406,11 @@ inline u64 near_bytes(unsigned n) {
                 4 * (u64)n);
 }
 
+// Workgroups that write the agents' words: no more than there are agents.
+inline unsigned obj_pack_blocks(unsigned N) {
+    return (unsigned)std::min<u64>(((u64)N + 2047) / 2048, 1024);
+}
+
 inline unsigned obj_blocks(unsigned M, unsigned R) {
     return (unsigned)(((u64)M + R + kObjTile - 1) / kObjTile);
 }
@@ -1433,14 +1471,17 @@ ss_status object_args(const uint32_t* obj_off, const uint32_t* obj_agents, uint3
     const u64 blocks = obj_blocks(n_objects, n_refs);
     A->carry = static_cast<ObjCarry*>(workspace);
     A->coord = reinterpret_cast<unsigned*>(A->carry + blocks);
-    A->w = reinterpret_cast<u64*>(A->coord + ((blocks + 1 + 3) & ~3ull));
+    // eight bytes an agent: its word, and room for the workgroups' flags
+    A->w = A->coord + ((blocks + 1 + 3) & ~3ull);
+    A->odd = A->w + n_agents;
+    A->odd_n = obj_pack_blocks(n_agents);
     return SS_OK;
 }
 
 hipError_t object_launch(const ObjArgs& A, hipStream_t st) {
     const unsigned blocks = obj_blocks(A.M, A.R);
     const unsigned part_blocks = (blocks + 1 + 15) / 16;
-    const unsigned pack_blocks = (unsigned)std::min<u64>(((u64)A.N + 2047) / 2048, 1024);
+    const unsigned pack_blocks = A.odd_n;
     hipLaunchKernelGGL(k_obj_prep, dim3(part_blocks + pack_blocks), dim3(256), 0, st, A,
                        blocks + 1, part_blocks);
     hipError_t e = hipGetLastError();
