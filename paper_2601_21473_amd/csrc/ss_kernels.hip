@@ -936,16 +936,30 @@ __device__ __forceinline__ void bt_tail(const BtArgs* Bp, unsigned n_v, unsigned
     bt_update_block(B, n_v, n_l, nF, units_in, units_out);
 }
 
-// Publish the plan to the host: every thread's host-visible writes are made
-// visible at system scope, then one thread writes the plan's sequence number
-// to the mapped flag word, which the host polls.  The fences only release:
-// nothing after them reads what the host writes (a full fence also
-// invalidates the L2 at system scope, in every wave).
+// Publish the plan to the host: one thread writes the plan's sequence number to
+// the mapped flag word, which the host polls, once every thread's host-visible
+// writes are complete.  Those are system-scope stores (host_store), which no
+// cache holds back, so each wave waits for its own and nothing is flushed: a
+// system-scope release would write back the whole L2, this plan's lists for
+// the device among it (publication at 64 agents 2.7 us so, 0.8 us
+// without).
 __device__ __forceinline__ void publish_plan(const PlanArgs& A) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (threadIdx.x == 0)
-        __hip_atomic_store(A.flag_host, A.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(A.flag_host, A.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+template <class T>
+__device__ __forceinline__ void host_store(T* p, T v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+__device__ __forceinline__ void host_store(PlanResult* p, const PlanResult& r) {
+    static_assert(sizeof(PlanResult) % 8 == 0, "whole words");
+    const u64* s = reinterpret_cast<const u64*>(&r);
+    u64* d = reinterpret_cast<u64*>(p);
+#pragma unroll
+    for (unsigned k = 0; k < sizeof(PlanResult) / 8; ++k) host_store(d + k, s[k]);
 }
 
 // The plan core: one workgroup of kCoreThreads threads; `lds` holds kLdsKeys
@@ -1014,7 +1028,7 @@ __device__ __forceinline__ void plan_core(const PlanArgs& A, u64* lds, CoreShare
             PlanResult r = {};
             r.status = 1;
             *A.res = r;
-            *A.res_host = r;
+            host_store(A.res_host, r);
             if (!kFused) *A.cnt = PlanCounters{};
         }
         publish_plan(A);
@@ -1258,7 +1272,7 @@ __device__ __forceinline__ void plan_core(const PlanArgs& A, u64* lds, CoreShare
     for (unsigned i = tid; i < n_l; i += blockDim.x) {
         const unsigned a = (unsigned)((i < nL ? A.sortL[i] : sortC[i - nL]) & idmask);
         A.loads[i] = a;
-        A.loads_host[i] = a;
+        host_store(A.loads_host + i, a);
         A.resident[a] = 1;
         if (i >= nL) A.loff[i + 1] = c.sum_demand + A.prefC[i - nL + 1];
     }
@@ -1269,9 +1283,9 @@ __device__ __forceinline__ void plan_core(const PlanArgs& A, u64* lds, CoreShare
         const unsigned v = (unsigned)(keysE[nT - 1 - i] & idmask);
         const unsigned char w = (!A.dirty || A.dirty[v]) ? 1 : 0;
         A.victims[i] = v;
-        A.victims_host[i] = v;
+        host_store(A.victims_host + i, v);
         A.vwritten[i] = w;
-        A.vwritten_host[i] = w;
+        host_store(A.vwritten_host + i, w);
         A.resident[v] = 0;
         *wunits = w ? (u64)units[v] : 0ull;
     };
@@ -1310,7 +1324,7 @@ __device__ __forceinline__ void plan_core(const PlanArgs& A, u64* lds, CoreShare
         r.n_free_used = n_free_used;
         r.units_written = A.woff[n_v];
         *A.res = r;
-        *A.res_host = r;
+        host_store(A.res_host, r);
         if (!kFused) *A.cnt = PlanCounters{};
     }
     publish_plan(A);
