@@ -715,13 +715,14 @@ __device__ __forceinline__ void free_scan_regs(const PlanArgs& A, u64 n_free_use
 constexpr unsigned kTagShift = 62;
 constexpr u64 kTagL = 1ull << kTagShift, kTagC = 2ull << kTagShift;
 constexpr u64 kKeyBits = kTagL - 1;
-constexpr unsigned kJointKeys = 1024 * kRegKeys;   // largest joint sort (LDS: twice this)
-static_assert(2 * kJointKeys <= (unsigned)kLdsKeys, "joint sort and its merge scratch fit");
+// Largest joint sort: its merge rounds take twice the keys, and so do, after it,
+// the keys with their unit prefixes and two leading zeros.
+constexpr unsigned kJointKeys = 1024 * kRegKeys - 1;
+static_assert(2 * 1024 * kRegKeys <= (unsigned)kLdsKeys && 2 * kJointKeys + 2 <= (unsigned)kLdsKeys,
+              "the joint sort and the prefixes fit");
 
-// Sorts lds[0..n) (tagged keys) and writes each set, untagged and ascending,
-// to its array: sortE[0..nT), sortL[0..nL), sortC[0..n - nT - nL).
-__device__ __forceinline__ void joint_sort_out(u64* lds, unsigned n, unsigned nT, unsigned nL,
-                                               u64* sortE, u64* sortL, u64* sortC) {
+// Sorts lds[0..n) (tagged keys) in place, lds[npad..2 npad) as scratch.
+__device__ __forceinline__ void joint_sort(u64* lds, unsigned n) {
     if (n == 0) return;
     const unsigned npad = pow2ceil(n);
     for (unsigned i = n + threadIdx.x; i < npad; i += kCoreThreads) {
@@ -730,12 +731,6 @@ __device__ __forceinline__ void joint_sort_out(u64* lds, unsigned n, unsigned nT
     }
     __syncthreads();
     merge_sort_lds_inl(lds, npad, n);
-    for (unsigned i = threadIdx.x; i < n; i += kCoreThreads) {
-        const u64 k = lds[i] & kKeyBits;
-        u64* dst = i < nT ? sortE + i : i < nT + nL ? sortL + (i - nT) : sortC + (i - nT - nL);
-        *dst = k;
-    }
-    __syncthreads();
 }
 
 // ---------------------------------------------------------------------------
@@ -1126,7 +1121,7 @@ __device__ __forceinline__ void plan_core(const PlanArgs& A, u64* lds, CoreShare
         }
         __syncthreads();
         m = S.uscal[6];
-        if (nT + nL + m <= kJointKeys) joint_sort_out(lds, nT + nL + m, nT, nL, A.sortE, A.sortL, A.sortC);
+        if (nT + nL + m <= kJointKeys) joint_sort(lds, nT + nL + m);
         else joint = false;
     }
     if (!joint) {
@@ -1139,27 +1134,39 @@ __device__ __forceinline__ void plan_core(const PlanArgs& A, u64* lds, CoreShare
             [&](u64* buf, unsigned cap, unsigned* counter) { gatherC(buf, cap, counter, 0); },
             A.sortC, lds, S);
     }
-    const u64* sortE = A.sortE;
-    const u64* sortC = A.sortC;
     // The three unit prefixes in one pass over the evictable keys in eviction
-    // order (descending), then the demand keys, then the candidates: prefE
-    // over the first, loff and prefC over the others, each from 0 (the bases
-    // are the units of the evictable set, HEsuf(b_E), and of the demand loads,
-    // sum_demand).  The keys come from the joint sort's LDS array where it ran
-    // (evictable keys at [0, nT), demand keys after them, then the candidates;
-    // tags lie above idmask).
-    {
-        const unsigned nTL = nT + nL;
-        const u64 baseL = units_T, baseC = units_T + c.sum_demand;
-        if (tid == 0) {
+    // order (descending), then the demand keys, then the candidates, each from
+    // 0 (the bases are the units of the evictable set, HEsuf(b_E), and of the
+    // demand loads, sum_demand).  After a joint sort the keys are in LDS
+    // (evictable keys at [0, nT), demand keys after them, then the candidates),
+    // and the prefixes of the first and last go behind them, so that nothing
+    // up to the lists reads global memory again (plan kernel at 64 agents 18.6
+    // us before, 17.5 so; at 10,000 37.6, 36.2); else both are in global memory.
+    const unsigned nTL = nT + nL, n = nTL + m;
+    const u64 baseL = units_T, baseC = units_T + c.sum_demand;
+    u64* pe_lds = lds + n;                           // [nT + 1], joint
+    u64* pc_lds = pe_lds + nT + 1;                   // [m + 1]
+    if (tid == 0) {
+        A.loff[0] = 0;
+        if (joint) {
+            pe_lds[0] = 0;
+            pc_lds[0] = 0;
+        } else {
             A.prefE[0] = 0;
-            A.loff[0] = 0;
             A.prefC[0] = 0;
         }
-        block_prefix_to(nTL + m, [&](unsigned i) {
-            u64 k;
-            if (joint) k = lds[i < nT ? nT - 1 - i : i];
-            else k = i < nT ? sortE[nT - 1 - i] : i < nTL ? A.sortL[i - nT] : sortC[i - nTL];
+    }
+    if (joint) {
+        block_prefix_to(n, [&](unsigned i) {
+            return (u64)units[lds[i < nT ? nT - 1 - i : i] & idmask];
+        }, [&](unsigned i, u64 v) {
+            if (i < nT) pe_lds[i + 1] = v;
+            else if (i < nTL) A.loff[i - nT + 1] = v - baseL;
+            else pc_lds[i - nTL + 1] = v - baseC;
+        }, S);
+    } else {
+        block_prefix_to(n, [&](unsigned i) {
+            const u64 k = i < nT ? A.sortE[nT - 1 - i] : i < nTL ? A.sortL[i - nT] : A.sortC[i - nTL];
             return (u64)units[k & idmask];
         }, [&](unsigned i, u64 v) {
             if (i < nT) A.prefE[i + 1] = v;
@@ -1169,55 +1176,47 @@ __device__ __forceinline__ void plan_core(const PlanArgs& A, u64* lds, CoreShare
     }
     stamp(2);
 
-    // demand victims: shortest prefix of the eviction order covering `need`.
-    // prefE is non-decreasing and prefE[nT] >= R >= need, so its length is the
-    // number of prefix values below need (prefE[0] = 0 among them): counted by
-    // the whole block instead of one thread's chain of dependent loads.
-    unsigned n_d = 0;
-    if (need > 0) {                                  // block-uniform
-        u64 below = 0;
+    // The rest of the plan on sorted keys (evictable E, demand L, candidates C)
+    // and prefixes (of E in eviction order, of C): compiled for LDS and for
+    // global memory, so that the LDS one uses LDS instructions.
+    PlanResult r = {};
+    auto decide = [&](const u64* E, const u64* L, const u64* C, const u64* pe,
+                      const u64* pc) __attribute__((always_inline)) {
+        // demand victims: shortest prefix of the eviction order covering `need`.
+        // pe is non-decreasing and pe[nT] >= R >= need, so its length is the
+        // number of prefix values below need (pe[0] = 0 among them): counted by
+        // the whole block instead of one thread's chain of dependent loads.
+        unsigned n_d = 0;
+        if (need > 0) {                              // block-uniform
+            u64 below = 0;
 #pragma unroll 4
-        for (unsigned i = tid; i < nT; i += blockDim.x) below += (long long)A.prefE[i] < need;
-        u64 tot;
-        (void)block_excl_scan(below, S, &tot);
-        n_d = (unsigned)tot;
-    }
-    const u64 free1 = free_before + A.prefE[n_d] - c.sum_demand;
+            for (unsigned i = tid; i < nT; i += blockDim.x) below += (long long)pe[i] < need;
+            u64 tot;
+            (void)block_excl_scan(below, S, &tot);
+            n_d = (unsigned)tot;
+        }
+        const u64 free1 = free_before + pe[n_d] - c.sum_demand;
+        if (tid == 0) S.uscal[3] = m;
+        __syncthreads();
+        stamp(3);
+        stamp(4);
 
-    stamp(3);
-
-    // acceptance: S_i <= budget and S_i <= free1 + (units of the remaining
-    // evictable residents with distance strictly larger than d_i)
-    if (tid == 0) S.uscal[3] = m;
-    // the evictable keys and their unit prefix in LDS for the searches below
-    // when both fit (the joint sort left the keys there; the sort buffer is
-    // free otherwise)
-    const bool in_lds = 2 * nT + 1 <= (unsigned)kLdsKeys;   // block-uniform
-    if (in_lds) {
-        if (!joint) for (unsigned i = tid; i < nT; i += blockDim.x) lds[i] = sortE[i];
-        for (unsigned i = tid; i <= nT; i += blockDim.x) lds[nT + i] = A.prefE[i];
-    }
-    const u64* keysE = in_lds ? lds : sortE;
-    const u64* pref = in_lds ? lds + nT : A.prefE;
-    __syncthreads();
-    stamp(4);
-    // (the search runs on LDS or on global memory; each instance sees which,
-    // so the LDS one uses LDS instructions)
-    auto accept = [&](const u64* keysE, const u64* pref) __attribute__((always_inline)) {
+        // acceptance: S_i <= budget and S_i <= free1 + (units of the remaining
+        // evictable residents with distance strictly larger than d_i).
         // kAccept candidates per thread at once: their binary searches run in
         // lockstep (ceil(log2(nT + 1)) steps), so the loads of one overlap the
         // others'
         constexpr unsigned kAccept = 4;
         const unsigned steps = nT ? 32u - (unsigned)__clz(nT) : 0u;
-        const u64 base_units = pref[n_d];
+        const u64 base_units = pe[n_d];
         for (unsigned i0 = tid; i0 < m; i0 += kAccept * blockDim.x) {
             u64 di[kAccept], Si[kAccept];
             unsigned lo[kAccept], hi[kAccept];
 #pragma unroll
             for (unsigned u = 0; u < kAccept; ++u) {
                 const unsigned i = i0 + u * blockDim.x;
-                di[u] = i < m ? sortC[i] >> idb : 0;
-                Si[u] = i < m ? A.prefC[i + 1] : 0;
+                di[u] = i < m ? (C[i] & kKeyBits) >> idb : 0;
+                Si[u] = i < m ? pc[i + 1] : 0;
                 lo[u] = 0;                           // first eviction index with d <= di
                 hi[u] = i < m ? nT : 0;
             }
@@ -1226,7 +1225,7 @@ __device__ __forceinline__ void plan_core(const PlanArgs& A, u64* lds, CoreShare
                 for (unsigned u = 0; u < kAccept; ++u) {
                     if (lo[u] < hi[u]) {
                         const unsigned mid = (lo[u] + hi[u]) >> 1;
-                        if ((keysE[nT - 1 - mid] >> idb) > di[u]) lo[u] = mid + 1;
+                        if ((E[nT - 1 - mid] >> idb) > di[u]) lo[u] = mid + 1;
                         else hi[u] = mid;
                     }
                 }
@@ -1237,92 +1236,98 @@ __device__ __forceinline__ void plan_core(const PlanArgs& A, u64* lds, CoreShare
                 // i) goes to one LDS atomic per wave: most candidates past the
                 // accepted prefix fail, and same-address atomics serialize
                 const unsigned i = i0 + u * blockDim.x;
-                const u64 G = lo[u] > n_d ? pref[lo[u]] - base_units : 0;
+                const u64 G = lo[u] > n_d ? pe[lo[u]] - base_units : 0;
                 const bool fail = i < m && !(Si[u] <= A.budget && Si[u] <= free1 + G);
                 const u64 fm = __ballot(fail);
                 if (fm && lane_id() == (unsigned)__ffsll((long long)fm) - 1)
                     atomicMin(&S.uscal[3], i);
             }
         }
-    };
-    if (in_lds) accept(lds, lds + nT);
-    else accept(sortE, A.prefE);
-    __syncthreads();
-    stamp(5);
-    const unsigned n_p = S.uscal[3];
-    // victims: the demand victims, extended while the accepted loads need
-    // room: to the first eviction index past n_d whose prefix reaches the
-    // target, i.e. n_d + 1 plus the prefix values below it (counted by the
-    // whole block), at most nT
-    unsigned n_v = n_d;
-    if (n_p > 0 && A.prefC[n_p] > free1) {           // block-uniform
-        const u64 target = pref[n_d] + (A.prefC[n_p] - free1);
-        u64 below = 0;
-#pragma unroll 4
-        for (unsigned i = n_d + 1 + tid; i < nT; i += blockDim.x) below += pref[i] < target;
-        u64 tot;
-        (void)block_excl_scan(below, S, &tot);
-        n_v = min(nT, n_d + 1 + (unsigned)tot);
-    }
-    const unsigned n_l = nL + n_p;
-    const u64 units_out = pref[n_v];
-    const u64 units_in = c.sum_demand + A.prefC[n_p];
-
-    // plan lists, load offsets, residency (victims and loads are disjoint)
-    for (unsigned i = tid; i < n_l; i += blockDim.x) {
-        const unsigned a = (unsigned)((i < nL ? A.sortL[i] : sortC[i - nL]) & idmask);
-        A.loads[i] = a;
-        host_store(A.loads_host + i, a);
-        A.resident[a] = 1;
-        if (i >= nL) A.loff[i + 1] = c.sum_demand + A.prefC[i - nL + 1];
-    }
-    // the victims, and the offsets of the written-back victims' units (all of
-    // them without a mask): with at most one victim per thread, from the same
-    // loads in one pass
-    auto victim = [&](unsigned i, u64* wunits) {
-        const unsigned v = (unsigned)(keysE[nT - 1 - i] & idmask);
-        const unsigned char w = (!A.dirty || A.dirty[v]) ? 1 : 0;
-        A.victims[i] = v;
-        host_store(A.victims_host + i, v);
-        A.vwritten[i] = w;
-        host_store(A.vwritten_host + i, w);
-        A.resident[v] = 0;
-        *wunits = w ? (u64)units[v] : 0ull;
-    };
-    if (n_v <= blockDim.x) {
-        u64 wv = 0;
-        if (tid < n_v) victim(tid, &wv);
-        u64 tot;
-        const u64 ex = block_excl_scan(wv, S, &tot);
-        if (tid == 0) A.woff[0] = 0;
-        if (tid < n_v) A.woff[tid + 1] = ex + wv;
         __syncthreads();
+        stamp(5);
+        const unsigned n_p = S.uscal[3];
+        // victims: the demand victims, extended while the accepted loads need
+        // room: to the first eviction index past n_d whose prefix reaches the
+        // target, i.e. n_d + 1 plus the prefix values below it (counted by the
+        // whole block), at most nT
+        unsigned n_v = n_d;
+        if (n_p > 0 && pc[n_p] > free1) {            // block-uniform
+            const u64 target = pe[n_d] + (pc[n_p] - free1);
+            u64 below = 0;
+#pragma unroll 4
+            for (unsigned i = n_d + 1 + tid; i < nT; i += blockDim.x) below += pe[i] < target;
+            u64 tot;
+            (void)block_excl_scan(below, S, &tot);
+            n_v = min(nT, n_d + 1 + (unsigned)tot);
+        }
+        const unsigned n_l = nL + n_p;
+
+        // plan lists, load offsets, residency (victims and loads are disjoint)
+        for (unsigned i = tid; i < n_l; i += blockDim.x) {
+            const unsigned a = (unsigned)((i < nL ? L[i] : C[i - nL]) & idmask);
+            host_store(A.loads_host + i, a);
+            A.loads[i] = a;
+            A.resident[a] = 1;
+            if (i >= nL) A.loff[i + 1] = c.sum_demand + pc[i - nL + 1];
+        }
+        // the victims with their eviction-order offsets, and the offsets of the
+        // written-back victims' units (all of them without a mask): with at
+        // most one victim per thread, from the same loads in one pass
+        auto victim = [&](unsigned i, u64* wunits) {
+            const unsigned v = (unsigned)(E[nT - 1 - i] & idmask);
+            const unsigned char w = (!A.dirty || A.dirty[v]) ? 1 : 0;
+            host_store(A.victims_host + i, v);
+            host_store(A.vwritten_host + i, w);
+            A.victims[i] = v;
+            A.vwritten[i] = w;
+            A.resident[v] = 0;
+            A.prefE[i] = pe[i];
+            *wunits = w ? (u64)units[v] : 0ull;
+        };
+        u64 written;
+        if (n_v <= blockDim.x) {
+            u64 wv = 0;
+            if (tid < n_v) victim(tid, &wv);
+            const u64 ex = block_excl_scan(wv, S, &written);
+            if (tid == 0) A.woff[0] = 0;
+            if (tid < n_v) A.woff[tid + 1] = ex + wv;
+        } else {
+            u64 wv;
+            for (unsigned i = tid; i < n_v; i += blockDim.x) victim(i, &wv);
+            block_prefix(n_v, [&](unsigned i) {
+                const unsigned v = (unsigned)(E[nT - 1 - i] & idmask);
+                return (!A.dirty || A.dirty[v]) ? (u64)units[v] : 0ull;
+            }, A.woff, S);
+            written = A.woff[n_v];
+        }
+        r.n_victims = n_v;
+        r.n_loads = n_l;
+        r.n_demand = nL;
+        r.n_demand_victims = n_d;
+        r.units_out = pe[n_v];
+        r.units_in = c.sum_demand + pc[n_p];
+        r.units_written = written;
+    };
+    if (joint) {
+        decide(lds, lds + nT, lds + nTL, pe_lds, pc_lds);
+    } else if (2 * nT + 1 <= (unsigned)kLdsKeys) {   // the evictable ones fit LDS (block-uniform)
+        for (unsigned i = tid; i < nT; i += blockDim.x) lds[i] = A.sortE[i];
+        for (unsigned i = tid; i <= nT; i += blockDim.x) lds[nT + i] = A.prefE[i];
+        __syncthreads();
+        decide(lds, A.sortL, A.sortC, lds + nT, A.prefC);
     } else {
-        u64 wv;
-        for (unsigned i = tid; i < n_v; i += blockDim.x) victim(i, &wv);
-        block_prefix(n_v, [&](unsigned i) {
-            const unsigned v = (unsigned)(keysE[nT - 1 - i] & idmask);
-            return (!A.dirty || A.dirty[v]) ? (u64)units[v] : 0ull;
-        }, A.woff, S);
+        decide(A.sortE, A.sortL, A.sortC, A.prefE, A.prefC);
     }
+    const unsigned n_v = r.n_victims, n_l = r.n_loads;
+    const u64 units_out = r.units_out, units_in = r.units_in;
 
     stamp(6);
     // pre-step free units, as many as the loads can use (the host needs only
     // their count)
     const u64 n_free_used = units_in < free_before ? units_in : free_before;
-    __syncthreads();
     if (tid == 0) {
-        PlanResult r = {};
-        r.status = 0;
-        r.n_victims = n_v;
-        r.n_loads = n_l;
-        r.n_demand = nL;
-        r.n_demand_victims = n_d;
-        r.units_out = units_out;
-        r.units_in = units_in;
         r.free_before = free_before;
         r.n_free_used = n_free_used;
-        r.units_written = A.woff[n_v];
         *A.res = r;
         host_store(A.res_host, r);
         if (!kFused) *A.cnt = PlanCounters{};
