@@ -722,6 +722,8 @@ static_assert(2 * 1024 * kRegKeys <= (unsigned)kLdsKeys && 2 * kJointKeys + 2 <=
               "the joint sort and the prefixes fit");
 
 // Sorts lds[0..n) (tagged keys) in place, lds[npad..2 npad) as scratch.
+// kSmall: n <= kCoreThreads (the longer register runs are not compiled).
+template <bool kSmall>
 __device__ __forceinline__ void joint_sort(u64* lds, unsigned n) {
     if (n == 0) return;
     const unsigned npad = pow2ceil(n);
@@ -730,7 +732,9 @@ __device__ __forceinline__ void joint_sort(u64* lds, unsigned n) {
         lds[npad + i] = ~0ull;                       // the merge rounds' second buffer
     }
     __syncthreads();
-    merge_sort_lds_inl(lds, npad, n);
+    if constexpr (!kSmall) merge_sort_lds_inl(lds, npad, n);
+    else if (npad <= 512) merge_sort_lds_e<1>(lds, npad, n);
+    else merge_sort_lds_e<2>(lds, npad, n);
 }
 
 // ---------------------------------------------------------------------------
@@ -770,6 +774,38 @@ __device__ __forceinline__ void classify_fused(const PlanArgs& A, CoreShared& S,
         b = nb;
     }
     flush_sums(t, &S.cnt);
+}
+
+// Classification of at most kCoreThreads agents, one per thread, for a plan
+// that sorts all of them (kSmall): the tagged keys of E, L and C straight into
+// keys[0 .. n_E + n_L + n_C[0]) in any order (the sort follows), the counts
+// and the sums the plan needs into S.cnt, and every agent's units into su, so
+// that nothing up to the plan's lists reads global memory again.
+__device__ __forceinline__ void classify_small(const PlanArgs& A, CoreShared& S, u64* keys,
+                                               unsigned* su) {
+    const unsigned a = threadIdx.x;
+    if ((a & ~63u) >= A.n) return;                   // wave-uniform: no agents
+    const bool v = a < A.n;
+    const unsigned D = v ? A.dist[a] : 0u, s = v ? A.units[a] : 0u;
+    const bool act = v && A.active[a], res = v && A.resident[a];
+    const AgentClass c = classify(A, a, v, D, act, res);
+    if (v) su[a] = s;
+    const bool in = c.isE || c.isL || c.isC;
+    const unsigned slot = wave_reserve(in, &S.uscal[7]);
+    if (in) keys[slot] = c.key | (c.isL ? kTagL : c.isC ? kTagC : 0ull);
+    const u64 e = __ballot(c.isE), l = __ballot(c.isL), k = __ballot(c.isC);
+    const u64 s_act = wave_sum(act ? (u64)s : 0), s_res = wave_sum(res ? (u64)s : 0);
+    const u64 s_dem = l ? wave_sum(c.isL ? (u64)s : 0) : 0;
+    const u64 s_evi = wave_sum(c.isE ? (u64)s : 0);
+    if (lane_id() == 0) {
+        if (e) atomicAdd(&S.cnt.n_E, (unsigned)__popcll(e));
+        if (l) atomicAdd(&S.cnt.n_L, (unsigned)__popcll(l));
+        if (k) atomicAdd(&S.cnt.n_C[0], (unsigned)__popcll(k));
+        if (s_act) atomicAdd(&S.cnt.sum_active, s_act);
+        if (s_res) atomicAdd(&S.cnt.sum_resident, s_res);
+        if (s_dem) atomicAdd(&S.cnt.sum_demand, s_dem);
+        if (s_evi) atomicAdd(&S.cnt.sum_evictable, s_evi);
+    }
 }
 
 // Items (victims or loads) of the block-table update handled together: every
@@ -988,7 +1024,12 @@ __device__ __forceinline__ void host_store(PlanResult* p, const PlanResult& r) {
 //    has free1 + G >= units(T) - need >= Cmax, which is what the test then
 //    computes from T as well.  (R <= 0: no victims, T is empty; HEsuf(0) < R:
 //    T is every evictable resident.)
-template <bool kFused>
+//
+// kSmall (at most kCoreThreads agents): all keys are sorted, so there are no
+// histograms, cuts or lists; the caller left the tagged keys at lds[0 ..) and
+// the units in S.histw (see classify_small).
+enum PlanMode { kMany, kFused, kSmall };
+template <PlanMode kMode>
 __device__ __forceinline__ void plan_core(const PlanArgs& A, u64* lds, CoreShared& S) {
     const unsigned tid = threadIdx.x;
     auto stamp = [&](int k) {
@@ -996,23 +1037,29 @@ __device__ __forceinline__ void plan_core(const PlanArgs& A, u64* lds, CoreShare
     };
     const u64 idmask = (1ull << A.idbits) - 1;
     const unsigned idb = A.idbits;
-    const unsigned* units = A.units;
+    const unsigned* su = reinterpret_cast<const unsigned*>(S.histw);
+    auto units_of = [&](unsigned a) { return (u64)(kMode == kSmall ? su[a] : A.units[a]); };
     unsigned* he_lds = reinterpret_cast<unsigned*>(lds);
     // the histograms and counters: this workgroup's LDS when it classified the
     // agents itself, else the global sums of all classifying workgroups (the
     // counters copied into LDS)
-    const u64* histw = kFused ? S.histw : A.hist_w;
-    const unsigned* histe = kFused ? he_lds : A.hist_e;
-    if (!kFused && tid == 0) S.cnt = *A.cnt;
+    const u64* histw = kMode == kFused ? S.histw : A.hist_w;
+    const unsigned* histe = kMode == kFused ? he_lds : A.hist_e;
+    if (kMode == kMany && tid == 0) S.cnt = *A.cnt;
     __syncthreads();
     const PlanCounters& c = S.cnt;
     stamp(1);
 
     static_assert(kDistBuckets == 2 * kCoreThreads, "two buckets per thread");
     const unsigned b0 = 2 * tid;
-    const u64 hc0 = histw[b0], hc1 = histw[b0 + 1];
-    const u64 he0 = histe[b0], he1 = histe[b0 + 1];
-    if (!kFused) {                                   // each thread clears what it read
+    u64 hc0 = 0, hc1 = 0, he0 = 0, he1 = 0;
+    if constexpr (kMode != kSmall) {
+        hc0 = histw[b0];
+        hc1 = histw[b0 + 1];
+        he0 = histe[b0];
+        he1 = histe[b0 + 1];
+    }
+    if (kMode == kMany) {                            // each thread clears what it read
         A.hist_w[b0] = 0;
         A.hist_w[b0 + 1] = 0;
         A.hist_e[b0] = 0;
@@ -1024,7 +1071,7 @@ __device__ __forceinline__ void plan_core(const PlanArgs& A, u64* lds, CoreShare
             r.status = 1;
             *A.res = r;
             host_store(A.res_host, r);
-            if (!kFused) *A.cnt = PlanCounters{};
+            if (kMode == kMany) *A.cnt = PlanCounters{};
         }
         publish_plan(A);
         stamp(8);
@@ -1034,105 +1081,114 @@ __device__ __forceinline__ void plan_core(const PlanArgs& A, u64* lds, CoreShare
     const long long need = (long long)c.sum_demand - (long long)free_before;
     const unsigned nE = c.n_E, nL = c.n_L;
 
-    // the cuts (see above): one scan of both histograms (packed into one word
-    // when their totals fit 32 bits), then the first bucket that fails and the
-    // first that does not reach R, each the minimum of a per-wave candidate
-    // (lanes hold ascending buckets) by one LDS atomic per wave
-    if (tid == 0) {
-        S.uscal[0] = kDistBuckets;
-        S.uscal[1] = kDistBuckets;
-    }
-    u64 hcb, heb, tot_c, tot_e;                      // HCbefore(b0), HEbefore(b0), totals
-    if (c.sum_cand < (1ull << 32) && c.sum_evictable < (1ull << 32)) {   // block-uniform
-        u64 tot;
-        const u64 x = block_excl_scan(((hc0 + hc1) << 32) | (he0 + he1), S, &tot);
-        hcb = x >> 32;
-        heb = x & 0xFFFFFFFFull;
-        tot_c = tot >> 32;
-        tot_e = tot & 0xFFFFFFFFull;
+    unsigned nT = 0, m = 0;                          // evictable residents and candidates sorted
+    u64 units_T = 0;                                 // the former's units
+    bool joint = true;
+    if constexpr (kMode == kSmall) {
+        nT = nE;
+        m = c.n_C[0];
+        units_T = c.sum_evictable;
+        joint_sort<true>(lds, nT + nL + m);
     } else {
-        hcb = block_excl_scan(hc0 + hc1, S, &tot_c);
-        heb = block_excl_scan(he0 + he1, S, &tot_e);
-    }
-    auto wave_first = [&](unsigned b, unsigned* dst) {
-        const u64 m = __ballot(b < kDistBuckets);
-        if (m && lane_id() == (unsigned)__ffsll((long long)m) - 1) atomicMin(dst, b);
-    };
-    const long long f1ub = need > 0 ? (long long)A.smax - 1 : -need;
-    auto fails = [&](u64 hc_before, u64 he_before) {
-        long long lim = (long long)(tot_e - he_before) - need;  // HEsuf(b) - need
-        if (lim < f1ub) lim = f1ub;
-        const u64 cap = A.budget < (u64)lim ? A.budget : (u64)lim;
-        return hc_before >= cap;                                // hc_before + 1 > cap
-    };
-    // the buckets that do not fail form the prefix [0, b_cut)
-    wave_first(fails(hcb, heb) ? b0 : fails(hcb + hc0, heb + he0) ? b0 + 1 : kDistBuckets,
-               &S.uscal[0]);
-    __syncthreads();
-    const unsigned b_cut = S.uscal[0];
-    if (b_cut < kDistBuckets && tid == b_cut / 2) S.wsum[0] = (b_cut & 1) ? hcb + hc0 : hcb;
-    __syncthreads();
-    const u64 hc_cut = b_cut < kDistBuckets ? S.wsum[0] : tot_c;       // HCbefore(b_cut)
-    const u64 cmax = A.budget < hc_cut ? A.budget : hc_cut;
-    const long long R = need + (long long)cmax;
-    unsigned b_E = kDistBuckets;                     // R <= 0: no victims
-    if (R > 0) {
-        // the buckets whose HEsuf reaches R form a prefix [0, b_E]
-        const u64 r = (u64)R;
-        wave_first(tot_e - heb < r ? b0 : tot_e - heb - he0 < r ? b0 + 1 : kDistBuckets,
-                   &S.uscal[1]);
-        __syncthreads();
-        const unsigned fr = S.uscal[1];
-        b_E = fr ? fr - 1 : 0;                       // none reaches R: every evictable resident
-        // units of the evictable residents of buckets >= b_E (the set sorted
-        // below): HEsuf(b_E), from the thread that holds bucket b_E
-        if (tid == b_E / 2) S.scal[0] = tot_e - ((b_E & 1) ? heb + he0 : heb);
-        __syncthreads();
-    }
-    const u64 units_T = b_E < kDistBuckets ? S.scal[0] : 0;
-
-    // The sorted sets: the evictable residents of buckets >= b_E (ascending;
-    // eviction order is descending key = the reversed array), the demand loads
-    // by id (their distance is 0, so key order is id order) and the candidates
-    // of buckets < b_cut, from the sub-lists whose distance range starts below
-    // b_cut.  Jointly in LDS when they fit (their counts are known once they
-    // are gathered), else one by one with the global-memory fallbacks.
-    auto keepT = [&](u64 k) { return dist_bucket((unsigned)(k >> idb)) >= b_E; };
-    auto keepC = [&](u64 k) { return dist_bucket((unsigned)(k >> idb)) < b_cut; };
-    auto gatherC = [&](u64* buf, unsigned cap, unsigned* counter, u64 tag) {
-        for (unsigned k = 0; k < kCandLists; ++k)
-            if (cand_list_start(k) < b_cut && c.n_C[k])
-                gather_keys(A.listC + (u64)k * A.n, c.n_C[k], keepC, buf, cap, counter, tag);
-    };
-    unsigned nT = 0, m = 0;
-    bool joint = idb + 32 <= kTagShift;              // kernel-uniform
-    if (joint) {
+        // the cuts (see above): one scan of both histograms (packed into one word
+        // when their totals fit 32 bits), then the first bucket that fails and the
+        // first that does not reach R, each the minimum of a per-wave candidate
+        // (lanes hold ascending buckets) by one LDS atomic per wave
         if (tid == 0) {
-            S.uscal[6] = 0;
-            S.uscal[7] = 0;
+            S.uscal[0] = kDistBuckets;
+            S.uscal[1] = kDistBuckets;
         }
-        __syncthreads();
-        if (b_E < kDistBuckets) gather_keys(A.listE, nE, keepT, lds, kJointKeys, &S.uscal[7]);
-        __syncthreads();
-        nT = S.uscal[7];
-        if (nT + nL <= kJointKeys) {                 // block-uniform
-            for (unsigned i = tid; i < nL; i += kCoreThreads) lds[nT + i] = A.listL[i] | kTagL;
-            gatherC(lds + nT + nL, kJointKeys - nT - nL, &S.uscal[6], kTagC);
+        u64 hcb, heb, tot_c, tot_e;                      // HCbefore(b0), HEbefore(b0), totals
+        if (c.sum_cand < (1ull << 32) && c.sum_evictable < (1ull << 32)) {   // block-uniform
+            u64 tot;
+            const u64 x = block_excl_scan(((hc0 + hc1) << 32) | (he0 + he1), S, &tot);
+            hcb = x >> 32;
+            heb = x & 0xFFFFFFFFull;
+            tot_c = tot >> 32;
+            tot_e = tot & 0xFFFFFFFFull;
+        } else {
+            hcb = block_excl_scan(hc0 + hc1, S, &tot_c);
+            heb = block_excl_scan(he0 + he1, S, &tot_e);
         }
+        auto wave_first = [&](unsigned b, unsigned* dst) {
+            const u64 m = __ballot(b < kDistBuckets);
+            if (m && lane_id() == (unsigned)__ffsll((long long)m) - 1) atomicMin(dst, b);
+        };
+        const long long f1ub = need > 0 ? (long long)A.smax - 1 : -need;
+        auto fails = [&](u64 hc_before, u64 he_before) {
+            long long lim = (long long)(tot_e - he_before) - need;  // HEsuf(b) - need
+            if (lim < f1ub) lim = f1ub;
+            const u64 cap = A.budget < (u64)lim ? A.budget : (u64)lim;
+            return hc_before >= cap;                                // hc_before + 1 > cap
+        };
+        // the buckets that do not fail form the prefix [0, b_cut)
+        wave_first(fails(hcb, heb) ? b0 : fails(hcb + hc0, heb + he0) ? b0 + 1 : kDistBuckets,
+                   &S.uscal[0]);
         __syncthreads();
-        m = S.uscal[6];
-        if (nT + nL + m <= kJointKeys) joint_sort(lds, nT + nL + m);
-        else joint = false;
-    }
-    if (!joint) {
-        select_sort(A.listL, nL, ~0ull, nL, A.sortL, lds, S);
-        nT = b_E >= kDistBuckets ? 0u : gather_sorted(
-            [&](u64* buf, unsigned cap, unsigned* counter) {
-                gather_keys(A.listE, nE, keepT, buf, cap, counter);
-            }, A.sortE, lds, S);
-        m = gather_sorted(
-            [&](u64* buf, unsigned cap, unsigned* counter) { gatherC(buf, cap, counter, 0); },
-            A.sortC, lds, S);
+        const unsigned b_cut = S.uscal[0];
+        if (b_cut < kDistBuckets && tid == b_cut / 2) S.wsum[0] = (b_cut & 1) ? hcb + hc0 : hcb;
+        __syncthreads();
+        const u64 hc_cut = b_cut < kDistBuckets ? S.wsum[0] : tot_c;       // HCbefore(b_cut)
+        const u64 cmax = A.budget < hc_cut ? A.budget : hc_cut;
+        const long long R = need + (long long)cmax;
+        unsigned b_E = kDistBuckets;                     // R <= 0: no victims
+        if (R > 0) {
+            // the buckets whose HEsuf reaches R form a prefix [0, b_E]
+            const u64 r = (u64)R;
+            wave_first(tot_e - heb < r ? b0 : tot_e - heb - he0 < r ? b0 + 1 : kDistBuckets,
+                       &S.uscal[1]);
+            __syncthreads();
+            const unsigned fr = S.uscal[1];
+            b_E = fr ? fr - 1 : 0;                       // none reaches R: every evictable resident
+            // units of the evictable residents of buckets >= b_E (the set sorted
+            // below): HEsuf(b_E), from the thread that holds bucket b_E
+            if (tid == b_E / 2) S.scal[0] = tot_e - ((b_E & 1) ? heb + he0 : heb);
+            __syncthreads();
+        }
+        units_T = b_E < kDistBuckets ? S.scal[0] : 0;
+
+        // The sorted sets: the evictable residents of buckets >= b_E (ascending;
+        // eviction order is descending key = the reversed array), the demand loads
+        // by id (their distance is 0, so key order is id order) and the candidates
+        // of buckets < b_cut, from the sub-lists whose distance range starts below
+        // b_cut.  Jointly in LDS when they fit (their counts are known once they
+        // are gathered), else one by one with the global-memory fallbacks.
+        auto keepT = [&](u64 k) { return dist_bucket((unsigned)(k >> idb)) >= b_E; };
+        auto keepC = [&](u64 k) { return dist_bucket((unsigned)(k >> idb)) < b_cut; };
+        auto gatherC = [&](u64* buf, unsigned cap, unsigned* counter, u64 tag) {
+            for (unsigned k = 0; k < kCandLists; ++k)
+                if (cand_list_start(k) < b_cut && c.n_C[k])
+                    gather_keys(A.listC + (u64)k * A.n, c.n_C[k], keepC, buf, cap, counter, tag);
+        };
+        joint = idb + 32 <= kTagShift;              // kernel-uniform
+        if (joint) {
+            if (tid == 0) {
+                S.uscal[6] = 0;
+                S.uscal[7] = 0;
+            }
+            __syncthreads();
+            if (b_E < kDistBuckets) gather_keys(A.listE, nE, keepT, lds, kJointKeys, &S.uscal[7]);
+            __syncthreads();
+            nT = S.uscal[7];
+            if (nT + nL <= kJointKeys) {                 // block-uniform
+                for (unsigned i = tid; i < nL; i += kCoreThreads) lds[nT + i] = A.listL[i] | kTagL;
+                gatherC(lds + nT + nL, kJointKeys - nT - nL, &S.uscal[6], kTagC);
+            }
+            __syncthreads();
+            m = S.uscal[6];
+            if (nT + nL + m <= kJointKeys) joint_sort<false>(lds, nT + nL + m);
+            else joint = false;
+        }
+        if (!joint) {
+            select_sort(A.listL, nL, ~0ull, nL, A.sortL, lds, S);
+            nT = b_E >= kDistBuckets ? 0u : gather_sorted(
+                [&](u64* buf, unsigned cap, unsigned* counter) {
+                    gather_keys(A.listE, nE, keepT, buf, cap, counter);
+                }, A.sortE, lds, S);
+            m = gather_sorted(
+                [&](u64* buf, unsigned cap, unsigned* counter) { gatherC(buf, cap, counter, 0); },
+                A.sortC, lds, S);
+        }
     }
     // The three unit prefixes in one pass over the evictable keys in eviction
     // order (descending), then the demand keys, then the candidates, each from
@@ -1158,7 +1214,7 @@ __device__ __forceinline__ void plan_core(const PlanArgs& A, u64* lds, CoreShare
     }
     if (joint) {
         block_prefix_to(n, [&](unsigned i) {
-            return (u64)units[lds[i < nT ? nT - 1 - i : i] & idmask];
+            return units_of((unsigned)(lds[i < nT ? nT - 1 - i : i] & idmask));
         }, [&](unsigned i, u64 v) {
             if (i < nT) pe_lds[i + 1] = v;
             else if (i < nTL) A.loff[i - nT + 1] = v - baseL;
@@ -1167,7 +1223,7 @@ __device__ __forceinline__ void plan_core(const PlanArgs& A, u64* lds, CoreShare
     } else {
         block_prefix_to(n, [&](unsigned i) {
             const u64 k = i < nT ? A.sortE[nT - 1 - i] : i < nTL ? A.sortL[i - nT] : A.sortC[i - nTL];
-            return (u64)units[k & idmask];
+            return units_of((unsigned)(k & idmask));
         }, [&](unsigned i, u64 v) {
             if (i < nT) A.prefE[i + 1] = v;
             else if (i < nTL) A.loff[i - nT + 1] = v - baseL;
@@ -1282,7 +1338,7 @@ __device__ __forceinline__ void plan_core(const PlanArgs& A, u64* lds, CoreShare
             A.vwritten[i] = w;
             A.resident[v] = 0;
             A.prefE[i] = pe[i];
-            *wunits = w ? (u64)units[v] : 0ull;
+            *wunits = w ? units_of(v) : 0ull;
         };
         u64 written;
         if (n_v <= blockDim.x) {
@@ -1296,7 +1352,7 @@ __device__ __forceinline__ void plan_core(const PlanArgs& A, u64* lds, CoreShare
             for (unsigned i = tid; i < n_v; i += blockDim.x) victim(i, &wv);
             block_prefix(n_v, [&](unsigned i) {
                 const unsigned v = (unsigned)(E[nT - 1 - i] & idmask);
-                return (!A.dirty || A.dirty[v]) ? (u64)units[v] : 0ull;
+                return (!A.dirty || A.dirty[v]) ? units_of(v) : 0ull;
             }, A.woff, S);
             written = A.woff[n_v];
         }
@@ -1330,7 +1386,7 @@ __device__ __forceinline__ void plan_core(const PlanArgs& A, u64* lds, CoreShare
         r.n_free_used = n_free_used;
         *A.res = r;
         host_store(A.res_host, r);
-        if (!kFused) *A.cnt = PlanCounters{};
+        if (kMode == kMany) *A.cnt = PlanCounters{};
     }
     publish_plan(A);
     stamp(7);
@@ -1409,7 +1465,28 @@ __global__ void __launch_bounds__(kCoreThreads) k_plan_core(PlanArgs A) {
     __syncthreads();
     classify_fused(A, S, he, he + kDistBuckets);
     __syncthreads();
-    plan_core<true>(fresh_args(), lds, S);
+    plan_core<kFused>(fresh_args(), lds, S);
+}
+
+// At most kCoreThreads agents: one per thread, all of them sorted.  Bound by the
+// workgroup's chain of barriers and dependent instructions, so it drops what a
+// small sort does not need: both histograms, the cuts and the lists in global
+// memory.  Whole kernel by k_plan_core and by this one: 64 agents 17.9 and 11.5
+// us, 256 19.0 and 13.9, 512 20.4 and 16.4, 1,024 23.3 and 20.0; the gain
+// shrinks as the sort grows by the keys that the cuts would leave out, and
+// more agents than threads would take several passes.
+__global__ void __launch_bounds__(kCoreThreads) k_plan_small(PlanArgs A) {
+    __shared__ u64 lds[2 * kCoreThreads + 2];        // keys and merge scratch, then the prefixes
+    __shared__ CoreShared S;
+    if (A.phase && threadIdx.x == 0) A.phase[0] = wall_clock64();
+    if (threadIdx.x == 0) {
+        S.cnt = PlanCounters{};
+        S.uscal[7] = 0;
+    }
+    __syncthreads();
+    classify_small(A, S, lds, reinterpret_cast<unsigned*>(S.histw));
+    __syncthreads();
+    plan_core<kSmall>(fresh_args(), lds, S);
 }
 
 // Classification over many workgroups, then the plan core in the workgroup
@@ -1491,7 +1568,7 @@ __global__ void __launch_bounds__(kCoreThreads) k_classify_core(PlanArgs A) {
     }
     __syncthreads();
     if (!S.uscal[3]) return;                         // workgroup-uniform
-    plan_core<false>(fresh_args(), lds, S);
+    plan_core<kMany>(fresh_args(), lds, S);
 }
 
 // ---------------------------------------------------------------------------
@@ -1609,7 +1686,9 @@ __global__ void k_zero_u32(unsigned* p, u64 n) {
 // ---------------------------------------------------------------------------
 
 hipError_t launch_plan(const PlanArgs& a, hipStream_t st) {
-    if (a.fused) {
+    if (a.n <= (unsigned)kCoreThreads) {
+        hipLaunchKernelGGL(k_plan_small, dim3(1), dim3(kCoreThreads), 0, st, a);
+    } else if (a.fused) {
         hipLaunchKernelGGL(k_plan_core, dim3(1), dim3(kCoreThreads), 0, st, a);
     } else {
         const unsigned per = kClassBatch * kCoreThreads;

@@ -9,6 +9,35 @@ from gpu_harness import S, run_parity
 pytestmark = pytest.mark.gpu
 
 
+def ragged_trace(n, per_step, seed, steps=14):
+    """per_step random agents of 1 to 4 units a step (none at step 5), a pool of
+    a third more than the largest step needs."""
+    rng = np.random.default_rng(seed)
+    units = rng.integers(1, 5, n).astype(np.uint32)
+    active = np.zeros((steps, n), np.uint8)
+    for t in range(steps):
+        if t != 5:
+            active[t, rng.choice(n, per_step, replace=False)] = 1
+    need = int((active.astype(np.int64) * units).sum(1).max())
+    pool = W.PoolSpec("syn", need + need // 3 + 1, [16], units)
+    dist = W.exact_distances(active)
+    return W.Trace(f"sets{n}", n, steps, [pool], active, dist, dist.copy(), {})
+
+
+# around a wave, the sort's register runs and one agent per thread of the
+# workgroup (1,024: the plan that sorts every agent; above it the cuts)
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 129, 512, 513, 1023, 1024, 1025])
+@pytest.mark.parametrize("theta,budget,dirty", [
+    (S, None, False), (6, 17, True), (0, None, False), (S, 0, True)])
+def test_small_plans(n, theta, budget, dirty):
+    tr = ragged_trace(n, max(1, n // 3), n)
+    mask = None
+    if dirty:                                   # some steps' victims partly written back
+        mask = (np.random.default_rng(n + 1).random((tr.n_steps, n)) < 0.5).astype(np.uint8)
+    run_parity(tr, theta=theta, budget=budget, slot_units=64, ring_slots=2, dirty=mask,
+               check_mirrors=True, label=f"small plan {n}, threshold {theta}, budget {budget}")
+
+
 # The union of the sets that a plan of n unit-size agents sorts is n keys here
 # (see the sets of test_joint_sort_sizes): the last union in LDS is 8,191 keys.
 @pytest.mark.parametrize("n", [8190, 8191, 8192, 8193])
