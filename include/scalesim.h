@@ -239,8 +239,9 @@ ss_status ss_plan_step(ss_pool* pool, const uint32_t* distances, const uint8_t* 
  * plane) into the eviction staging ring with the pack kernel and copies each
  * such victim's bytes to its host copy, ring slot by ring slot: with
  * hipMemcpyAsync, or by one kernel per slot where the victims' bytes are few
- * (1 MiB each on average, host copies device-mapped and 16-byte aligned).  Clean victims (dirty mask) are not copied.  Returns once
- * queued.  SS_ERR_ORDER unless called right after ss_plan_step. */
+ * (1 MiB each on average, host copies device-mapped, 16-byte aligned and apart
+ * from each other; agents that share one write it in eviction order).  Clean
+ * victims (dirty mask) are not copied.  Returns once queued.  SS_ERR_ORDER unless called right after ss_plan_step. */
 ss_status ss_evict_pack(ss_pool* pool, void* stream);
 
 /* Load (Appendix A, Load(memObj, agentIDs, ...)): copies every loaded agent's

@@ -134,6 +134,7 @@ struct ss_pool {
     u64 direct_bytes = 0;          // directions of at most this many bytes go direct
     char* host_dev = nullptr;      // device address of the host copies, or null
     bool link_ok = false;          // every host copy is device-mapped and 16-byte aligned
+    bool host_shared = false;      // some agents' host copies overlap
 
     // device metadata
     unsigned* d_units = nullptr;
@@ -487,6 +488,19 @@ void host_offsets(ss_pool* p) {
     }
 }
 
+// Whether some agents' host copies overlap.
+bool copies_overlap(const ss_pool* p) {
+    std::vector<u64> at(p->N);
+    for (u64 a = 0; a < p->N; ++a) at[a] = a;
+    auto before = [&](u64 a, u64 b) { return p->host_off[a] < p->host_off[b]; };
+    if (!std::is_sorted(p->host_off.begin(), p->host_off.end()))
+        std::sort(at.begin(), at.end(), before);
+    for (u64 i = 0; i + 1 < p->N; ++i)
+        if (p->host_off[at[i]] + (u64)p->s[at[i]] * p->unit_bytes > p->host_off[at[i + 1]])
+            return true;
+    return false;
+}
+
 // Whether a staged direction of `units` units of `agents` agents moves its
 // slots by k_link: their runs are short, and every slot's words count in 32 bits.
 bool by_link(const ss_pool* p, u64 units, u64 agents) {
@@ -735,6 +749,7 @@ ss_status ss_pool_create(const ss_pool_desc* d, ss_pool** out) {
         // unit_bytes is a multiple of 16, so aligned offsets align every word
         p->link_ok = reinterpret_cast<uintptr_t>(p->host_dev) % 16 == 0;
         for (u64 off : p->host_off) p->link_ok = p->link_ok && off % 16 == 0;
+        p->host_shared = copies_overlap(p);
         CREATE_TRY(dalloc(&p->d_host_off, N));
         CREATE_TRY(dalloc(&p->d_whost, U));
         CREATE_TRY(dalloc(&p->d_lhost, U));
@@ -1135,7 +1150,8 @@ ss_status ss_evict_pack(ss_pool* p, void* stream) {
         if (timing) TRY_HIP(p, hipEventRecord(tp->b, so), true);
         TRY_HIP(p, hipEventRecord(p->ev_packed[0], so), true);
     }
-    const bool link = !direct && by_link(p, total, p->n_written);
+    // victims that share a host copy write it in eviction order: one copy each
+    const bool link = !direct && !p->host_shared && by_link(p, total, p->n_written);
     size_t vi = 0;
     for (u64 k = 0; !direct && k < nslots; ++k) {
         const u64 p0 = k * ups, p1 = std::min(total, p0 + ups);

@@ -80,6 +80,49 @@ def test_unaligned_host_copies():
     assert np.array_equal(got[0][1], got[1][1])
 
 
+@pytest.mark.parametrize("shift", [0, 1])       # copies shared whole, or overlapping by half
+def test_shared_host_copies(shift):
+    """Victims that share a host copy write it in eviction order: the last one's
+    bytes stay."""
+    units = np.full(64, 2, np.uint32)
+    spec = W.PoolSpec("kv", 64, [4 * KIB], units)
+    mem = PoolMemory(spec, 2 * 2 * 256 * spec.unit_bytes, 2)
+    content = W.Content(spec, seed=2)
+    fill_host(mem, content, spec)
+    start = mem.host_np.copy()
+    args = mem.desc_args()
+    off = np.uint64(spec.unit_bytes) * (np.uint64(shift) * (np.arange(64, dtype=np.uint64) % 8))
+    args["host_off"] = off
+    pool = B.Pool(**args)
+    try:
+        dist, act = np.full(64, 9, np.uint32), np.zeros(64, np.uint8)
+        act[:32] = 1
+        plans, held = [], None
+        for t in range(2):                      # the first half in, then out for the second
+            plans.append(pool.plan_step(dist.ctypes.data, act.ctypes.data, 0))
+            pool.evict_pack()
+            if t == 0:
+                pool.prefetch_unpack()
+                pool.sync()
+                table = pool.block_table_host_all()[:64]    # units of the agents in the pool
+                held = np.random.default_rng(4).integers(0, 256, (64, spec.unit_bytes), np.uint8)
+                plane = np.empty_like(held)
+                plane[table] = held
+                mem.planes[0].upload(plane)
+                act = 1 - act
+        pool.sync()
+        want = start.copy()
+        held = held.reshape(32, -1)             # by agent
+        for v in plans[1]["victims"]:
+            at = int(off[v])
+            want[at:at + held.shape[1]] = held[v]
+        assert len(plans[1]["victims"]) == 32
+        assert np.array_equal(mem.host_np, want)
+    finally:
+        pool.close()
+        mem.free()
+
+
 @pytest.mark.parametrize("chunks,slot_units", [
     ([16], 3), ([48, 1040], 5), ([64 * KIB] * 2, 16), ([64 * KIB] * 2, 17)])   # 2 MiB and above
 def test_loader_chunks(chunks, slot_units):
