@@ -203,8 +203,11 @@ __global__ void __launch_bounds__(kObjThreads) k_obj_min(ObjArgs A, unsigned n_t
     constexpr unsigned kXcds = 8;
     const unsigned tid = threadIdx.x;
     const unsigned total = A.M + A.R;
-    unsigned flags = 0;                              // any set: see k_obj_prep
-    for (unsigned k = __lane_id(); k < A.odd_n; k += 64) flags |= A.odd[k];
+    // any flag set: see k_obj_prep.  The first read stands outside the loop, so
+    // that it is in flight with the tile's own reads (324,160 references of small
+    // trees, a call: 14.5 us with every read in the loop, 14.4 so).
+    unsigned flags = __lane_id() < A.odd_n ? A.odd[__lane_id()] : 0u;
+    for (unsigned k = __lane_id() + 64; k < A.odd_n; k += 64) flags |= A.odd[k];
     const unsigned xcd = blockIdx.x % kXcds, per_xcd = gridDim.x / kXcds;
     const unsigned q = n_tiles / kXcds, rem = n_tiles % kXcds;
     const unsigned t_lo = xcd < rem ? xcd * (q + 1) : rem * (q + 1) + (xcd - rem) * q;
