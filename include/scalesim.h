@@ -100,7 +100,13 @@ typedef struct {
     const uint64_t* host_off;       /* [N] byte offset of each agent's host copy (copied);
                                        NULL = packed, agent after agent. Offsets may alias
                                        (agents then share one host copy, as when one
-                                       physical adapter serves many logical ones).       */
+                                       physical adapter serves many logical ones).
+                                       Victims of a step that share one write it in
+                                       eviction order.  A load that shares one with a
+                                       written-back victim of its step reads it after the
+                                       victim where both directions are within
+                                       direct_bytes, else before, while or after it is
+                                       written (the directions overlap).                 */
     uint64_t        host_bytes;     /* size of host_backing; every copy must fit           */
     void*           dev_staging;    /* device buffer (caller-owned): first half stages
                                        evictions, second half stages loads               */
@@ -115,7 +121,9 @@ typedef struct {
                                        latency of each copy dominates; larger steps use the
                                        staged pipeline.  When both directions of a step
                                        are direct and non-empty they run as one launch
-                                       (each released unit written back, then loaded).
+                                       (each released unit written back, then loaded),
+                                       unless their host copies overlap.  Written-back
+                                       victims that share a host copy are staged.
                                        0 = always staged.  host_backing must then be
                                        device-accessible pinned memory.  (The load
                                        scheduler ignores it.)                             */
@@ -240,8 +248,9 @@ ss_status ss_plan_step(ss_pool* pool, const uint32_t* distances, const uint8_t* 
  * such victim's bytes to its host copy, ring slot by ring slot: with
  * hipMemcpyAsync, or by one kernel per slot where the victims' bytes are few
  * (1 MiB each on average, host copies device-mapped, 16-byte aligned and apart
- * from each other; agents that share one write it in eviction order).  Clean
- * victims (dirty mask) are not copied.  Returns once queued.  SS_ERR_ORDER unless called right after ss_plan_step. */
+ * from each other).  Victims that share a host copy write it in eviction order.
+ * Clean victims (dirty mask) are not copied.  Returns once queued.
+ * SS_ERR_ORDER unless called right after ss_plan_step. */
 ss_status ss_evict_pack(ss_pool* pool, void* stream);
 
 /* Load (Appendix A, Load(memObj, agentIDs, ...)): copies every loaded agent's

@@ -51,6 +51,7 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <utility>
 #include <vector>
 
 using namespace ss;
@@ -135,6 +136,8 @@ struct ss_pool {
     char* host_dev = nullptr;      // device address of the host copies, or null
     bool link_ok = false;          // every host copy is device-mapped and 16-byte aligned
     bool host_shared = false;      // some agents' host copies overlap
+    std::vector<std::pair<u64, u64>> ranges;   // with host_shared: room for N (step_overlap)
+    bool loads_after = false;      // this step's loads wait for its evictions
 
     // device metadata
     unsigned* d_units = nullptr;
@@ -501,6 +504,34 @@ bool copies_overlap(const ss_pool* p) {
     return false;
 }
 
+// Which host copies of a step overlap: some of its written-back victims' among
+// each other, and some of its loads' with those.
+struct StepOverlap {
+    bool victims = false, loads = false;
+};
+StepOverlap step_overlap(ss_pool* p) {
+    StepOverlap o;
+    if (!p->host_shared) return o;
+    typedef std::pair<u64, u64> Range;
+    auto range = [&](unsigned a) {
+        return Range(p->host_off[a], p->host_off[a] + (u64)p->s[a] * p->unit_bytes);
+    };
+    std::vector<Range>& out = p->ranges;
+    out.clear();
+    for (unsigned i = 0; i < p->res.n_victims; ++i)
+        if (p->h_vwritten[i]) out.push_back(range(p->h_victims[i]));
+    std::sort(out.begin(), out.end());
+    for (size_t i = 0; i + 1 < out.size() && !o.victims; ++i)
+        o.victims = out[i].second > out[i + 1].first;
+    // as far as the victims' copies are apart they end in order too
+    for (unsigned i = 0; i < p->res.n_loads && !o.victims && !o.loads; ++i) {
+        const Range l = range(p->h_loads[i]);
+        const auto next = std::lower_bound(out.begin(), out.end(), Range(l.second, 0));
+        o.loads = next != out.begin() && std::prev(next)->second > l.first;
+    }
+    return o;
+}
+
 // Whether a staged direction of `units` units of `agents` agents moves its
 // slots by k_link: their runs are short, and every slot's words count in 32 bits.
 bool by_link(const ss_pool* p, u64 units, u64 agents) {
@@ -750,6 +781,7 @@ ss_status ss_pool_create(const ss_pool_desc* d, ss_pool** out) {
         p->link_ok = reinterpret_cast<uintptr_t>(p->host_dev) % 16 == 0;
         for (u64 off : p->host_off) p->link_ok = p->link_ok && off % 16 == 0;
         p->host_shared = copies_overlap(p);
+        if (p->host_shared) p->ranges.reserve(N);
         CREATE_TRY(dalloc(&p->d_host_off, N));
         CREATE_TRY(dalloc(&p->d_whost, U));
         CREATE_TRY(dalloc(&p->d_lhost, U));
@@ -1061,7 +1093,11 @@ ss_status ss_evict_pack(ss_pool* p, void* stream) {
     hipStream_t caller = static_cast<hipStream_t>(stream);
     const u64 total = p->res.units_written;
     const u64 ups = p->units_per_slot;
-    const bool direct = p->direct_bytes && total && total * p->unit_bytes <= p->direct_bytes;
+    const bool small = p->direct_bytes && total && total * p->unit_bytes <= p->direct_bytes;
+    // Victims that share a host copy write it in eviction order, which one
+    // launch does not keep: they take the staged pipeline.
+    const StepOverlap overlap = small ? step_overlap(p) : StepOverlap{};
+    const bool direct = small && !overlap.victims;
     // A step whose moves are all direct (or empty) runs on the caller's
     // stream: block-table update, pack and unpack queue behind the plan on one
     // hardware queue, without the cross-queue waits that cost more than such
@@ -1072,8 +1108,10 @@ ss_status ss_evict_pack(ss_pool* p, void* stream) {
     p->inline_step = p->direct_bytes && (total == 0 || direct) && (total_in == 0 || direct_in);
     // Both directions direct and non-empty: one launch moves both (k_duplex),
     // so the link carries them at once instead of one after the other (the
-    // loads mostly reuse the units the victims release).
-    p->duplex_step = p->inline_step && direct && direct_in && p->d_rhost;
+    // loads mostly reuse the units the victims release), unless a load reads
+    // what a victim writes: then the loads' launch follows the evictions'.
+    p->duplex_step = p->inline_step && direct && direct_in && p->d_rhost && !overlap.loads;
+    p->loads_after = overlap.victims && direct_in;
     hipStream_t so = p->inline_step ? caller : p->st_out;
     st = collect_plan_timing(p);
     if (st) return st;
@@ -1212,6 +1250,7 @@ ss_status ss_prefetch_unpack(ss_pool* p, void* stream) {
         TRY_HIP(p, hipEventRecord(p->ev_caller, caller), true);
         TRY_HIP(p, hipStreamWaitEvent(p->st_in, p->ev_caller, 0), true);
     }
+    if (p->loads_after) TRY_HIP(p, hipStreamWaitEvent(si, p->ev_out_done, 0), true);
     // the unpacks write units the block-table update assigns (as in
     // ss_evict_pack, the wait is implied when the plan ran on this stream)
     if (caller != p->bt_stream) TRY_HIP(p, hipStreamWaitEvent(si, bt_event(p), 0), true);

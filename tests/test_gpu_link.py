@@ -149,3 +149,55 @@ def test_loader_chunks(chunks, slot_units):
         loader.close()
         d_to.free()
         mem.free()
+
+
+@pytest.mark.parametrize("layout", ["one copy", "half apart", "pairs"])
+@pytest.mark.parametrize("loads", [False, True])
+def test_shared_host_copies_direct(layout, loads):
+    """Direct steps: victims that share a host copy write it in eviction order,
+    and the step's loads read it after them.  The copies: one for all agents;
+    four, each overlapping the next by half; one for every two agents, so that
+    only a victim and a load share."""
+    n, s = 256, 2
+    units = np.full(n, s, np.uint32)
+    spec = W.PoolSpec("kv", n, [4 * KIB], units)
+    size = s * spec.unit_bytes
+    mem = PoolMemory(spec, 2 * 2 * n * spec.unit_bytes, 2)
+    fill_host(mem, W.Content(spec, seed=2), spec)
+    want = mem.host_np.copy()
+    args = mem.desc_args()
+    a = np.arange(n, dtype=np.uint64)
+    args["host_off"] = {"one copy": a * 0, "half apart": a % 4 * np.uint64(size // 2),
+                        "pairs": a % (n // 2) * np.uint64(size)}[layout]
+    off = args["host_off"].astype(np.int64)
+    pool = B.Pool(**args, direct_bytes=4 << 20)
+    try:
+        act = np.zeros((2, n), np.uint8)
+        act[0, :n // 2] = 1                     # the first half in, then out for the second
+        act[1, n // 2:] = 1
+        dist = np.full(n, 9, np.uint32)
+        pool.plan_step(dist.ctypes.data, act[0].ctypes.data, 0)
+        pool.evict_pack()
+        pool.prefetch_unpack()
+        pool.sync()
+        table = pool.block_table_host_all().reshape(n, s)
+        held = np.random.default_rng(4).integers(0, 256, (n, spec.unit_bytes), np.uint8)
+        mem.planes[0].upload(held)
+        plan = pool.plan_step(dist.ctypes.data, act[1].ctypes.data, 0)
+        assert len(plan["victims"]) == n // 2 and len(plan["loads"]) == n // 2
+        pool.evict_pack()
+        if loads:
+            pool.prefetch_unpack()
+        pool.sync()
+        for v in plan["victims"]:
+            want[off[v]:off[v] + size] = held[table[v]].reshape(-1)
+        assert np.array_equal(mem.host_np, want)
+        if not loads:
+            return
+        table = pool.block_table_host_all().reshape(n, s)
+        got = mem.units_bytes(table[plan["loads"]].reshape(-1)).reshape(-1, size)
+        exp = np.stack([want[off[b]:off[b] + size] for b in plan["loads"]])
+        assert np.array_equal(got, exp)
+    finally:
+        pool.close()
+        mem.free()
