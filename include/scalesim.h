@@ -364,8 +364,8 @@ ss_status ss_probe_object_distances(const uint32_t* obj_off, const uint32_t* obj
  * The search is queued on `stream` (two ordinary launches; beyond 4,194,304
  * vertices a cooperative one besides); the call returns without waiting.  The
  * 32-bit word at workspace offset 20 is 1 after the search if a wait between
- * levels ever exceeded its bound (the hop counts are then incomplete); it stays
- * 0 otherwise.  n_vertices and n_edges must be
+ * levels ever exceeded its bound, which grows with the graph (the hop counts are
+ * then incomplete); it stays 0 otherwise.  n_vertices and n_edges must be
  * below 2^31; offsets that break the rules above give unspecified hop counts
  * but no access outside the arrays.  SS_ERR_ARG for NULL, too small or
  * non-device arguments, SS_ERR_HIP if the device has no cooperative launch or
@@ -375,6 +375,16 @@ ss_status ss_hop_distances(const uint32_t* row_off, const uint32_t* col, uint32_
                            uint32_t n_edges, const uint32_t* sources, uint32_t n_sources,
                            uint32_t max_hops, uint32_t* hops, void* workspace,
                            uint64_t workspace_bytes, void* stream);
+
+/* Test probe: ss_hop_distances as when the device holds few of its workgroups
+ * at a time (at most `workgroups` >= 1 are launched; no effect beyond 4,194,304
+ * vertices) and with `polls` in the place of the part of a wait's bound that
+ * does not grow with the graph.  On the null stream, synchronous.  Other
+ * arguments, errors and results as ss_hop_distances. */
+ss_status ss_probe_hop_distances(const uint32_t* row_off, const uint32_t* col, uint32_t n_vertices,
+                                 uint32_t n_edges, const uint32_t* sources, uint32_t n_sources,
+                                 uint32_t max_hops, uint32_t* hops, void* workspace,
+                                 uint64_t workspace_bytes, uint32_t workgroups, uint32_t polls);
 
 /* Interaction distances (Section 3.2, interaction-involved simulations:
  * D = min(D_action, D_interaction), D_interaction = physical distance /

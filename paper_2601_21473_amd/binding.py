@@ -41,7 +41,7 @@ EXPORTS = ["ss_pool_create", "ss_pool_destroy", "ss_plan_step", "ss_evict_pack",
            "ss_event_destroy", "ss_event_record", "ss_event_elapsed", "ss_loader_create",
            "ss_loader_destroy", "ss_loader_submit", "ss_loader_pump", "ss_loader_pending",
            "ss_loader_sync", "ss_loader_get_stats", "ss_debug_fail_copy",
-           "ss_interaction_distances_static"]
+           "ss_interaction_distances_static", "ss_probe_hop_distances"]
 
 
 class ss_load_task(C.Structure):
@@ -167,6 +167,8 @@ def load():
         "ss_hop_distances_workspace": ([C.c_uint32], C.c_uint64),
         "ss_hop_distances": ([P, P, C.c_uint32, C.c_uint32, P, C.c_uint32, C.c_uint32, P, P,
                               C.c_uint64, P], C.c_int32),
+        "ss_probe_hop_distances": ([P, P, C.c_uint32, C.c_uint32, P, C.c_uint32, C.c_uint32, P, P,
+                                    C.c_uint64, C.c_uint32, C.c_uint32], C.c_int32),
         "ss_debug_fail_copy": ([C.c_uint32], None),
         "ss_interaction_distances_static": ([P, P, C.c_uint32, C.c_uint32, C.c_uint32, P, P],
                                             C.c_int32),
@@ -460,6 +462,16 @@ def hop_distances(row_off: int, col: int, n_vertices: int, n_edges: int, sources
     _check(load().ss_hop_distances(int(row_off), int(col), int(n_vertices), int(n_edges),
                                    int(sources), int(n_sources), int(max_hops), int(hops),
                                    int(workspace), int(workspace_bytes), int(stream)))
+
+
+def probe_hop_distances(row_off: int, col: int, n_vertices: int, n_edges: int, sources: int,
+                        n_sources: int, max_hops: int, hops: int, workspace: int,
+                        workspace_bytes: int, workgroups: int, polls: int):
+    """``ss_probe_hop_distances`` (test probe; synchronous)."""
+    _check(load().ss_probe_hop_distances(int(row_off), int(col), int(n_vertices), int(n_edges),
+                                         int(sources), int(n_sources), int(max_hops), int(hops),
+                                         int(workspace), int(workspace_bytes), int(workgroups),
+                                         int(polls)))
 
 
 def interaction_distances_workspace(n_agents: int) -> int:

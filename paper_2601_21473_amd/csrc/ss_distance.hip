@@ -333,7 +333,11 @@ constexpr int kBfsThreads = 1024;
 constexpr int kBfsEdges = 8;                 // edges claimed per vertex per round
 constexpr int kBfsVerts = 2;                 // frontier vertices per lane per round
 constexpr unsigned kBfsBatch = 8;            // vertices per lane that a sweep reads at once
-constexpr unsigned kBfsSpin = 1u << 22;      // bound of a wait (about 5 s)
+// Bound of a wait of both searches, in polls of about a microsecond: what the
+// longest level takes grows with the graph (one lane takes 0.45 us an edge of a
+// vertex with very many), so the bound does too.
+constexpr u64 kHopPolls = 1u << 24;
+inline u64 hop_polls(u64 base, unsigned V, unsigned E) { return base + V + 2 * (u64)E; }
 
 struct BfsArgs {
     const unsigned* row_off;                 // [V + 1]
@@ -345,6 +349,7 @@ struct BfsArgs {
     u64* hint;                               // [V / 64 + 1] visited vertices, or null
     unsigned chunks;                         // chunks per level
     unsigned span;                           // vertices per chunk, a multiple of kBfsThreads
+    u64 polls;                               // bound of a wait
 };
 constexpr int kCtlTicket = 4;                // chunks given out
 constexpr int kCtlError = 5;                 // 1 if a wait hit its bound
@@ -516,9 +521,9 @@ __global__ void __launch_bounds__(kBfsThreads) k_bfs(BfsArgs A) {
                 if (s_own[0] == 0 && from == 0)
                     __hip_atomic_store(&done[(level + kBfsSlots / 2) % kBfsSlots], 0ull,
                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                for (unsigned spin = 0; (unsigned)v < A.chunks; ++spin) {
+                for (u64 spin = 0; (unsigned)v < A.chunks; ++spin) {
                     if (level == 0 && spin % kBfsPatience == kBfsPatience - 1 && draw()) break;
-                    if (spin > kBfsSpin) {
+                    if (spin > A.polls) {
                         __hip_atomic_store(&A.ctl[kCtlError], 1u, __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_AGENT);
                         state = 2;
@@ -550,7 +555,6 @@ constexpr unsigned kBfsSweep = 1u << 22;
 constexpr int kQueueThreads = 256;
 constexpr int kQueueEdges = 8;               // edges claimed per vertex per round
 constexpr int kQueueVerts = 2;               // frontier vertices per thread per round
-constexpr unsigned kQueueSpin = 1u << 24;    // barrier spin bound (about 0.5 s)
 
 struct QueueArgs {
     const unsigned* row_off;                 // [V + 1]
@@ -561,6 +565,7 @@ struct QueueArgs {
     uint2* q0;                               // [V] frontier queues: edge ranges
     uint2* q1;
     unsigned* ctl;                           // [8] see kCtl*
+    u64 polls;                               // bound of a wait
 };
 constexpr int kQueueCnt = 0;                   // [0..2] queue lengths, rotating
 constexpr int kQueueBarCount = 3;              // grid barrier arrivals
@@ -576,7 +581,7 @@ constexpr int kQueueLevels = 6;                // levels expanded
 // acquire fence when it changes.  Returns false for every thread of a
 // workgroup whose wait exceeded the bound; the caller then leaves the kernel,
 // so every wave exits.
-__device__ bool grid_barrier(unsigned* ctl) {
+__device__ bool grid_barrier(unsigned* ctl, u64 polls) {
     __shared__ int s_ok;
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -591,10 +596,10 @@ __device__ bool grid_barrier(unsigned* ctl) {
             __hip_atomic_store(&ctl[kQueueBarCount], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             __hip_atomic_fetch_add(&ctl[kQueueBarGen], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         } else {
-            unsigned spin = 0;
+            u64 spin = 0;
             while (__hip_atomic_load(&ctl[kQueueBarGen], __ATOMIC_RELAXED,
                                      __HIP_MEMORY_SCOPE_AGENT) == gen) {
-                if (++spin > kQueueSpin) {
+                if (++spin > polls) {
                     ok = 0;
                     __hip_atomic_store(&ctl[kQueueError], 1u, __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_AGENT);
@@ -725,7 +730,7 @@ __global__ void __launch_bounds__(kQueueThreads) k_queue(QueueArgs A) {
                 }
             }
         }
-        if (!grid_barrier(A.ctl)) return;
+        if (!grid_barrier(A.ctl, A.polls)) return;
     }
 }
 
@@ -1597,10 +1602,16 @@ uint64_t ss_hop_distances_workspace(uint32_t n_vertices) {
     return 64 + 2 * (((uint64_t)n_vertices * 8 + 255) & ~255ull);
 }
 
-ss_status ss_hop_distances(const uint32_t* row_off, const uint32_t* col, uint32_t n_vertices,
-                           uint32_t n_edges, const uint32_t* sources, uint32_t n_sources,
-                           uint32_t max_hops, uint32_t* hops, void* workspace,
-                           uint64_t workspace_bytes, void* stream) {
+}  // extern "C"
+
+namespace {
+
+// ss_hop_distances with `base` polls of every wait's bound independent of the
+// graph, and for up to kBfsSweep vertices at most `most` workgroups.
+ss_status hop_call(const uint32_t* row_off, const uint32_t* col, uint32_t n_vertices,
+                   uint32_t n_edges, const uint32_t* sources, uint32_t n_sources,
+                   uint32_t max_hops, uint32_t* hops, void* workspace, uint64_t workspace_bytes,
+                   unsigned most, u64 base, void* stream) {
     if (n_vertices >= (1u << 31) || n_edges >= (1u << 31))
         return set_err(SS_ERR_ARG, "n_vertices and n_edges must be below 2^31");
     if (n_vertices == 0) return SS_OK;
@@ -1628,7 +1639,8 @@ ss_status ss_hop_distances(const uint32_t* row_off, const uint32_t* col, uint32_
         return queue_launch({row_off, col, sources, n_vertices, n_edges, n_sources, max_hops, hops,
                              reinterpret_cast<uint2*>(ws + 64),
                              reinterpret_cast<uint2*>(ws + 64 + qbytes),
-                             reinterpret_cast<unsigned*>(ws)}, dev, st);
+                             reinterpret_cast<unsigned*>(ws),
+                             hop_polls(base, n_vertices, n_edges)}, dev, st);
     }
     int cus = 256;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
@@ -1645,6 +1657,7 @@ ss_status ss_hop_distances(const uint32_t* row_off, const uint32_t* col, uint32_
     A.max_hops = max_hops;
     A.hops = hops;
     A.ctl = reinterpret_cast<unsigned*>(ws);
+    A.polls = hop_polls(base, n_vertices, n_edges);
     // claims that fail cost more than the hint's read once a level has many
     if (n_vertices >= 32768) A.hint = reinterpret_cast<u64*>(ws + 4 * kCtlWords);
     // chunks of 1,024 vertices, from 96 chunks on of up to 4,096, at most one
@@ -1661,10 +1674,35 @@ ss_status ss_hop_distances(const uint32_t* row_off, const uint32_t* col, uint32_
                        dim3(kBfsThreads), 0, st, A);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) {
-        hipLaunchKernelGGL(k_bfs, dim3(A.chunks), dim3(kBfsThreads), 0, st, A);
+        hipLaunchKernelGGL(k_bfs, dim3(std::min(A.chunks, most)), dim3(kBfsThreads), 0, st, A);
         e = hipGetLastError();
     }
     if (e != hipSuccess) return set_err(SS_ERR_HIP, "hop distance kernels: %s", hipGetErrorString(e));
+    return SS_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
+ss_status ss_hop_distances(const uint32_t* row_off, const uint32_t* col, uint32_t n_vertices,
+                           uint32_t n_edges, const uint32_t* sources, uint32_t n_sources,
+                           uint32_t max_hops, uint32_t* hops, void* workspace,
+                           uint64_t workspace_bytes, void* stream) {
+    return hop_call(row_off, col, n_vertices, n_edges, sources, n_sources, max_hops, hops,
+                    workspace, workspace_bytes, kBfsMost, kHopPolls, stream);
+}
+
+ss_status ss_probe_hop_distances(const uint32_t* row_off, const uint32_t* col, uint32_t n_vertices,
+                                 uint32_t n_edges, const uint32_t* sources, uint32_t n_sources,
+                                 uint32_t max_hops, uint32_t* hops, void* workspace,
+                                 uint64_t workspace_bytes, uint32_t workgroups, uint32_t polls) {
+    if (workgroups < 1) return set_err(SS_ERR_ARG, "workgroups must be >= 1");
+    ss_status r = hop_call(row_off, col, n_vertices, n_edges, sources, n_sources, max_hops, hops,
+                           workspace, workspace_bytes, workgroups, polls, nullptr);
+    if (r != SS_OK || n_vertices == 0) return r;
+    const hipError_t e = hipStreamSynchronize(nullptr);
+    if (e != hipSuccess) return set_err(SS_ERR_HIP, "hop distance probe: %s", hipGetErrorString(e));
     return SS_OK;
 }
 

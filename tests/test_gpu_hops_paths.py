@@ -12,7 +12,8 @@ pytestmark = pytest.mark.gpu
 NEVER = 0xFFFFFFFF
 
 
-def gpu_hops(off, col, src, max_hops=NEVER, calls=2):
+def gpu_hops(off, col, src, max_hops=NEVER, calls=2, probe=None):
+    """``probe``: (workgroups, polls) of ``probe_hop_distances``."""
     v, e = len(off) - 1, len(col)
     bufs = [DeviceBuffer(4 * (v + 1)), DeviceBuffer(max(4, 4 * e)), DeviceBuffer(max(4, 4 * len(src))),
             DeviceBuffer(4 * v)]
@@ -25,8 +26,12 @@ def gpu_hops(off, col, src, max_hops=NEVER, calls=2):
         ws.upload(np.full(min(wsb, 1 << 20), 0x77, np.uint8))
         out = []
         for _ in range(calls):                  # the second call finds the first one's workspace
-            B.hop_distances(bufs[0].ptr, bufs[1].ptr, v, e, bufs[2].ptr, len(src), max_hops,
-                            bufs[3].ptr, ws.ptr, wsb)
+            args = (bufs[0].ptr, bufs[1].ptr, v, e, bufs[2].ptr, len(src), max_hops, bufs[3].ptr,
+                    ws.ptr, wsb)
+            if probe:
+                B.probe_hop_distances(*args, *probe)
+            else:
+                B.hop_distances(*args)
             out.append(bufs[3].download(0, 4 * v).view(np.uint32))
             assert ws.download(20, 4).view(np.uint32)[0] == 0
         for h in out[1:]:
@@ -72,3 +77,18 @@ def test_very_large_ring(v):
     w = 120_000
     got = gpu_hops(np.arange(v + 1), (np.arange(v) + w) % v, np.arange(w), calls=1)
     assert np.array_equal(got, np.arange(v) // w)
+
+
+@pytest.mark.parametrize("v", [2048, 5000, 40_000])
+def test_wait_bound_grows_with_the_graph(v):
+    """A vertex of a million edges keeps its workgroup longer than any wait
+    bound without regard to the graph would allow here (0 polls): the others
+    wait for it all the same."""
+    rng = np.random.default_rng(v)
+    deg = np.full(v, 2)
+    deg[v // 2] = 1_000_000
+    off = np.concatenate([[0], np.cumsum(deg)])
+    col = rng.integers(0, v, off[-1])
+    print(f"[hops] v={v} hub, 0 polls", flush=True)
+    got = gpu_hops(off, col, [v // 2], calls=1, probe=(512, 0))
+    assert np.array_equal(got, hop_distances(off, col, np.array([v // 2]), None))
