@@ -144,8 +144,17 @@ __host__ __device__ inline unsigned dist_bucket(unsigned d) {
     return 1024u + 32u * (p - 10u) + ((d >> (p - 5u)) & 31u);
 }
 
-constexpr int kPlanPhases = 10;
+// Sort keys are (distance << idbits) | id.  Where distance and id take at most
+// kTagShift bits, a joint sort's keys carry their set in the bits above.
+constexpr unsigned kTagShift = 62;
+constexpr u64 kTagL = 1ull << kTagShift, kTagC = 2ull << kTagShift;
+// The distance of a key with or without a tag: its 32 bits end where a tag, if
+// there is one, may begin.  (Keys of more than 2^30 agents take all 63 bits.)
+__host__ __device__ inline unsigned key_distance(u64 key, unsigned idbits) {
+    return (unsigned)(key >> idbits);
+}
 
+constexpr int kPlanPhases = 10;
 
 struct CopyArgs {
     const int* units_list;          // vunits (pack) or lunits (unpack)

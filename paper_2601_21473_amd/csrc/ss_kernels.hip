@@ -711,10 +711,8 @@ __device__ __forceinline__ void free_scan_regs(const PlanArgs& A, u64 n_free_use
 // then L, then C, so one merge sort replaces three (each sort's rounds are
 // barrier- and latency-bound on one workgroup, so three small sorts cost
 // about three times one sort of their union).  Keys are below
-// 2^(32 + idbits), so the tags fit when idbits <= kTagShift - 32.
-constexpr unsigned kTagShift = 62;
-constexpr u64 kTagL = 1ull << kTagShift, kTagC = 2ull << kTagShift;
-constexpr u64 kKeyBits = kTagL - 1;
+// 2^(32 + idbits), so the tags (kTagL, kTagC) fit when idbits <= kTagShift - 32.
+//
 // Largest joint sort: its merge rounds take twice the keys, and so do, after it,
 // the keys with their unit prefixes and two leading zeros.
 constexpr unsigned kJointKeys = 1024 * kRegKeys - 1;
@@ -1153,8 +1151,8 @@ __device__ __forceinline__ void plan_core(const PlanArgs& A, u64* lds, CoreShare
         // of buckets < b_cut, from the sub-lists whose distance range starts below
         // b_cut.  Jointly in LDS when they fit (their counts are known once they
         // are gathered), else one by one with the global-memory fallbacks.
-        auto keepT = [&](u64 k) { return dist_bucket((unsigned)(k >> idb)) >= b_E; };
-        auto keepC = [&](u64 k) { return dist_bucket((unsigned)(k >> idb)) < b_cut; };
+        auto keepT = [&](u64 k) { return dist_bucket(key_distance(k, idb)) >= b_E; };
+        auto keepC = [&](u64 k) { return dist_bucket(key_distance(k, idb)) < b_cut; };
         auto gatherC = [&](u64* buf, unsigned cap, unsigned* counter, u64 tag) {
             for (unsigned k = 0; k < kCandLists; ++k)
                 if (cand_list_start(k) < b_cut && c.n_C[k])
@@ -1266,12 +1264,13 @@ __device__ __forceinline__ void plan_core(const PlanArgs& A, u64* lds, CoreShare
         const unsigned steps = nT ? 32u - (unsigned)__clz(nT) : 0u;
         const u64 base_units = pe[n_d];
         for (unsigned i0 = tid; i0 < m; i0 += kAccept * blockDim.x) {
-            u64 di[kAccept], Si[kAccept];
+            u64 Si[kAccept];
+            unsigned di[kAccept];
             unsigned lo[kAccept], hi[kAccept];
 #pragma unroll
             for (unsigned u = 0; u < kAccept; ++u) {
                 const unsigned i = i0 + u * blockDim.x;
-                di[u] = i < m ? (C[i] & kKeyBits) >> idb : 0;
+                di[u] = i < m ? key_distance(C[i], idb) : 0;
                 Si[u] = i < m ? pc[i + 1] : 0;
                 lo[u] = 0;                           // first eviction index with d <= di
                 hi[u] = i < m ? nT : 0;
@@ -1281,7 +1280,7 @@ __device__ __forceinline__ void plan_core(const PlanArgs& A, u64* lds, CoreShare
                 for (unsigned u = 0; u < kAccept; ++u) {
                     if (lo[u] < hi[u]) {
                         const unsigned mid = (lo[u] + hi[u]) >> 1;
-                        if ((E[nT - 1 - mid] >> idb) > di[u]) lo[u] = mid + 1;
+                        if (key_distance(E[nT - 1 - mid], idb) > di[u]) lo[u] = mid + 1;
                         else hi[u] = mid;
                     }
                 }
