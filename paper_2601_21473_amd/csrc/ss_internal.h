@@ -50,6 +50,13 @@ struct PlanResult {
     u64 units_written;          // victims' units written back
 };
 
+// An object's 64-bit words (a copy: its members are not read as other types).
+template <class T>
+__host__ __device__ inline void words_of(const T& v, u64 (&w)[sizeof(T) / 8]) {
+    static_assert(sizeof(T) % 8 == 0, "whole words");
+    __builtin_memcpy(w, &v, sizeof(T));
+}
+
 // One wave-sized piece of a unit: `len` bytes of plane `plane`, starting at
 // `chunk_off` inside the plane's chunk and at `unit_off` inside the unit's
 // serialised bytes (planes concatenated in order).

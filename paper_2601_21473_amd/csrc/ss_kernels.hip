@@ -984,11 +984,11 @@ __device__ __forceinline__ void host_store(T* p, T v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 __device__ __forceinline__ void host_store(PlanResult* p, const PlanResult& r) {
-    static_assert(sizeof(PlanResult) % 8 == 0, "whole words");
-    const u64* s = reinterpret_cast<const u64*>(&r);
+    u64 w[sizeof(PlanResult) / 8];
+    words_of(r, w);
     u64* d = reinterpret_cast<u64*>(p);
 #pragma unroll
-    for (unsigned k = 0; k < sizeof(PlanResult) / 8; ++k) host_store(d + k, s[k]);
+    for (unsigned k = 0; k < sizeof(PlanResult) / 8; ++k) host_store(d + k, w[k]);
 }
 
 // The plan core: one workgroup of kCoreThreads threads; `lds` holds kLdsKeys
