@@ -758,6 +758,13 @@ __device__ __forceinline__ unsigned pack_pos(int x, int y) {
     return ((unsigned)x & 0x7FFFu) | (((unsigned)y & 0x7FFFu) << 16);
 }
 
+// Agent j's position, by one read; callers' arrays are only 4-byte aligned.
+__device__ __forceinline__ int2 position(const int* __restrict__ pos, u64 j) {
+    int q[2];
+    __builtin_memcpy(q, pos + 2 * j, sizeof q);
+    return make_int2(q[0], q[1]);
+}
+
 __device__ __forceinline__ unsigned isqrt_u32(unsigned x) {
     unsigned r = (unsigned)sqrt((double)x);
     while ((u64)r * r > x) --r;
@@ -797,9 +804,8 @@ __global__ void __launch_bounds__(64 * kPairWaves) k_pair(PairArgs A) {
     const unsigned l = threadIdx.x & 63u, part = l / kOwn;
     const unsigned w = (unsigned)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const unsigned i = blockIdx.x * kOwn + l % kOwn;
-    const int2* __restrict__ pos = reinterpret_cast<const int2*>(A.pos);
     // past the end the last agent of all, whose repeats change no minimum
-    auto load = [&](unsigned j) { return pos[min(j, A.n - 1)]; };
+    auto load = [&](unsigned j) { return position(A.pos, min(j, A.n - 1)); };
     const int2 own = load(i);
     const unsigned pi = pack_pos(own.x, own.y), groups = (A.n + 63) / 64u;
     unsigned best = kNone;
@@ -913,12 +919,11 @@ __global__ void __launch_bounds__(1024) k_near_blocks(NearArgs A) {
         count[c] = make_uint4(0, 0, 0, 0);
     if (blockIdx.x == 0 && t == 0) *A.alloc = 0;
     __syncthreads();
-    const int2* __restrict__ pos = reinterpret_cast<const int2*>(A.pos);
     for (u64 i0 = blockIdx.x * 1024u; i0 < A.n; i0 += step) {      // workgroup-uniform
         const bool valid = i0 + t < A.n;
         unsigned b = 0;
         if (valid) {
-            const int2 q = pos[i0 + t];
+            const int2 q = position(A.pos, i0 + t);
             b = near_block_of(pack_pos(q.x, q.y));
         }
         // the first lane's block by one addition of all its lanes (a town
@@ -996,7 +1001,7 @@ __global__ void __launch_bounds__(kNearThreads) k_near_count(NearArgs A) {
     const bool valid = i < A.n;
     unsigned c = 0, p = 0, slot = 0, r = 0;
     if (valid) {
-        const int2 q = reinterpret_cast<const int2*>(A.pos)[i];
+        const int2 q = position(A.pos, i);
         p = pack_pos(q.x, q.y);
         const NearGrid g(A.block[near_block_of(p)]);
         c = min(g.cell((p & (kNearTiles - 1)) >> g.sx, ((p >> 16) & (kNearTiles - 1)) >> g.sy),
@@ -1082,7 +1087,7 @@ __global__ void __launch_bounds__(kNearThreads) k_near_place(NearArgs A) {
     if (i >= A.n) return;
     const unsigned c = A.cell[i], r = A.rank[i];
     if (c >= A.cells) return;
-    const int2 q = reinterpret_cast<const int2*>(A.pos)[i];
+    const int2 q = position(A.pos, i);
     const unsigned at = A.first[c] + (r & ~kNearShared);
     if (at >= A.n) return;
     A.spos[at] = pack_pos(q.x, q.y);

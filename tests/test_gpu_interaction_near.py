@@ -82,6 +82,27 @@ def test_nearest_agent(n, kind):
             b.free()
 
 
+@pytest.mark.parametrize("n", [1, 700, NEAR + 5])
+def test_positions_at_any_word(n):
+    """Positions on a 4-byte boundary that is no 8-byte one: both paths."""
+    rng = np.random.default_rng(n)
+    pos = np.ascontiguousarray(places("even", n, rng), dtype=np.int32)
+    d_act = np.full(n, 60, np.uint32)
+    exp = expected(pos, d_act, 1, 0) if n > 1 else d_act
+    p, d, out = DeviceBuffer(8 * n + 4), DeviceBuffer(4 * n), DeviceBuffer(4 * n)
+    full = B.interaction_distances_workspace(n)
+    ws = DeviceBuffer(full)
+    try:
+        p.upload(pos.reshape(-1), 4)
+        d.upload(d_act)
+        for size in (4 * n, full):
+            B.interaction_distances(p.ptr + 4, d.ptr, n, 1, 0, out.ptr, ws.ptr, size)
+            assert np.array_equal(out.download(0, 4 * n).view(np.uint32), exp)
+    finally:
+        for b in (p, d, out, ws):
+            b.free()
+
+
 def test_short_workspace_is_refused():
     n = NEAR
     b = DeviceBuffer(16 * n)
