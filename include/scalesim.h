@@ -201,8 +201,10 @@ typedef struct {                    /* cumulative since create or ss_reset_stats
 
 /* Create a pool (Appendix A: register a memory module).  Validates every
  * descriptor field, copies the host arrays, allocates the library's device
- * metadata (block table, state, plan buffers; O(N + U + sum(s)) bytes) and its
- * streams.  The pool starts empty.  Returns SS_ERR_ARG (message in
+ * metadata (block table, state, plan buffers; O(N + U + sum(s)) bytes, of which
+ * 16 U + 8 N for host-copy offsets in a pool with direct_bytes, and in one whose
+ * smallest agent has at most 1 MiB and whose copies are 16-byte aligned if they
+ * can be had) and its streams.  The pool starts empty.  Returns SS_ERR_ARG (message in
  * ss_last_error) for an invalid descriptor, SS_ERR_HIP / SS_ERR_NOMEM on
  * runtime failures; *out is set only on SS_OK. */
 ss_status ss_pool_create(const ss_pool_desc* desc, ss_pool** out);

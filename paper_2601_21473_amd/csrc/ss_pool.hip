@@ -134,8 +134,10 @@ struct ss_pool {
     u64 slot_bytes = 0;
     u64 direct_bytes = 0;          // directions of at most this many bytes go direct
     char* host_dev = nullptr;      // device address of the host copies, or null
-    bool link_ok = false;          // every host copy is device-mapped and 16-byte aligned
-    bool host_shared = false;      // some agents' host copies overlap
+    bool link_ok = false;          // every host copy is device-mapped and 16-byte aligned, some
+                                   // agent's bytes are few enough for k_link, and every
+                                   // slot's words count in 32 bits
+    bool host_shared = false;      // some agents' host copies overlap (if link_ok or direct)
     std::vector<std::pair<u64, u64>> ranges;   // with host_shared: room for N (step_overlap)
     bool loads_after = false;      // this step's loads wait for its evictions
 
@@ -155,8 +157,8 @@ struct ss_pool {
     int *d_vunits = nullptr, *d_lunits = nullptr, *d_free_old = nullptr, *d_wunits = nullptr;
     unsigned char* d_vwritten = nullptr;
     u64* d_woff = nullptr;
-    u64* d_host_off = nullptr;     // with host_dev: [N] host-copy offsets
-    u64 *d_whost = nullptr, *d_lhost = nullptr;   // with host_dev: [U] per moved unit
+    u64* d_host_off = nullptr;     // link_ok or direct mode: [N] host-copy offsets
+    u64 *d_whost = nullptr, *d_lhost = nullptr;   // link_ok or direct mode: [U] per moved unit
     u64* d_rhost = nullptr;                       // direct mode: [U] per released position
     unsigned* d_wrel = nullptr;                   // direct mode: [U] per written-back position
     PlanResult* d_res = nullptr;
@@ -533,10 +535,9 @@ StepOverlap step_overlap(ss_pool* p) {
 }
 
 // Whether a staged direction of `units` units of `agents` agents moves its
-// slots by k_link: their runs are short, and every slot's words count in 32 bits.
+// slots by k_link: their runs are short.
 bool by_link(const ss_pool* p, u64 units, u64 agents) {
-    return p->link_ok && units * p->unit_bytes <= agents * kLinkRunBytes &&
-           p->slot_bytes / 16 < (1ull << 31);
+    return p->link_ok && units * p->unit_bytes <= agents * kLinkRunBytes;
 }
 
 LinkArgs link_args(const ss_pool* p, char* slot, const u64* off, u64 first, u64 units) {
@@ -777,16 +778,32 @@ ss_status ss_pool_create(const ss_pool_desc* d, ss_pool** out) {
         }
     }
     if (p->host_dev) {
-        // unit_bytes is a multiple of 16, so aligned offsets align every word
-        p->link_ok = reinterpret_cast<uintptr_t>(p->host_dev) % 16 == 0;
+        // unit_bytes is a multiple of 16, so aligned offsets align every word; no
+        // mean is below the smallest agent's bytes
+        const u64 least = *std::min_element(p->s.begin(), p->s.end()) * p->unit_bytes;
+        p->link_ok = reinterpret_cast<uintptr_t>(p->host_dev) % 16 == 0 &&
+                     least <= kLinkRunBytes && p->slot_bytes / 16 < (1ull << 31);
         for (u64 off : p->host_off) p->link_ok = p->link_ok && off % 16 == 0;
+    }
+    if (p->link_ok || p->direct_bytes) {
         p->host_shared = copies_overlap(p);
         if (p->host_shared) p->ranges.reserve(N);
-        CREATE_TRY(dalloc(&p->d_host_off, N));
-        CREATE_TRY(dalloc(&p->d_whost, U));
-        CREATE_TRY(dalloc(&p->d_lhost, U));
-        CREATE_TRY(hipMemcpy(p->d_host_off, p->host_off.data(), N * sizeof(u64),
-                             hipMemcpyHostToDevice));
+        e = dalloc(&p->d_host_off, N);
+        if (e == hipSuccess) e = dalloc(&p->d_whost, U);
+        if (e == hipSuccess) e = dalloc(&p->d_lhost, U);
+        if (e == hipSuccess) {
+            CREATE_TRY(hipMemcpy(p->d_host_off, p->host_off.data(), N * sizeof(u64),
+                                 hipMemcpyHostToDevice));
+        } else if (p->direct_bytes) {
+            CREATE_TRY(e);
+        } else {                                     // no room: copies do without them
+            (void)hipGetLastError();
+            for (u64** d : {&p->d_host_off, &p->d_whost, &p->d_lhost}) {
+                if (*d) (void)hipFree(*d);
+                *d = nullptr;
+            }
+            p->link_ok = false;
+        }
     }
     if (p->direct_bytes) {
         CREATE_TRY(dalloc(&p->d_rhost, U));

@@ -1,6 +1,8 @@
 """Short runs over the host link: the kernel that takes the place of per-agent
 copies (k_link) and the loader's unpack straight from the host copy, against the
 oracle at the sizes where they can go wrong."""
+import ctypes as C
+
 import numpy as np
 import pytest
 
@@ -200,4 +202,37 @@ def test_shared_host_copies_direct(layout, loads):
         assert np.array_equal(got, exp)
     finally:
         pool.close()
+        mem.free()
+
+
+def device_free():
+    """Bytes free on the device, from the HIP runtime that the library runs on."""
+    hip = C.CDLL("libamdhip64.so")
+    free, total = C.c_size_t(), C.c_size_t()
+    assert hip.hipMemGetInfo(C.byref(free), C.byref(total)) == 0
+    return free.value
+
+
+@pytest.mark.parametrize("form,lists", [("short", True), ("long", False), ("unaligned", False)])
+def test_offset_lists_only_where_they_serve(form, lists):
+    """Host-copy offsets (16 bytes a unit) are kept on the device only by pools
+    whose steps can go by k_link: not if every agent has more than 1 MiB, nor with
+    copies off the 16-byte grid."""
+    capacity = 8 << 20
+    units = np.full(4, (1 << 16) + (form == "long"), np.uint32)
+    spec = W.PoolSpec("kv", capacity, [16], units)
+    mem = PoolMemory(spec, 2 * 1024 * 16, 1)
+    args = mem.desc_args()
+    if form == "unaligned":
+        args["host_off"] = mem.host_off + np.uint64(8)
+        args["host_off"][-1] -= np.uint64(8)
+    try:
+        B.Pool(**args).close()                  # the shared streams and their memory
+        before = device_free()
+        pool = B.Pool(**args)
+        used = before - device_free()
+        pool.close()
+        plain = 4 * 4 * capacity                # the plan's unit lists, whatever the form
+        assert used >= plain + 16 * capacity if lists else used < plain + 8 * capacity, used
+    finally:
         mem.free()
