@@ -92,3 +92,58 @@ def test_wait_bound_grows_with_the_graph(v):
     print(f"[hops] v={v} hub, 0 polls", flush=True)
     got = gpu_hops(off, col, [v // 2], calls=1, probe=(512, 0))
     assert np.array_equal(got, hop_distances(off, col, np.array([v // 2]), None))
+
+
+def communities(v, size, degree, seed):
+    """Edges inside blocks of ``size`` consecutive vertices, and from every 64th
+    vertex one into the next block."""
+    rng = np.random.default_rng(seed)
+    col = (np.arange(v) // size * size)[:, None] + rng.integers(0, size, (v, degree))
+    col[::64, 0] = np.arange(0, v, 64) + size
+    return np.arange(v + 1) * degree, np.minimum(col, v - 1)
+
+
+@pytest.mark.parametrize("v,size", [(30_000, 500), (300_000, 4096), (300_000, 70_000)])
+def test_communities(v, size):
+    """Levels that lie close together in the vertices' numbers."""
+    off, col = communities(v, size, 6, v)
+    col = col.reshape(-1)
+    for src in ([0], [v // 2, 5]):
+        got = gpu_hops(off, col, src)
+        assert np.array_equal(got, hop_distances(off, col, np.array(src), None))
+
+
+def test_time_does_not_depend_on_the_numbering():
+    """A search whose levels lie close together takes at most twice as long as
+    over the same graph with its vertices numbered at random (it took four times
+    as long where every level was the work of one or two workgroups)."""
+    v, degree = 1 << 22, 8
+    off, col = communities(v, 16384, degree, 1)
+    to = np.random.default_rng(2).permutation(v)
+    mixed = np.empty_like(col)
+    mixed[to] = to[col]
+    ms, hops = [], []
+    timer = B.EventTimer()
+    for c, s in ((col, 0), (mixed, to[0])):
+        bufs = [DeviceBuffer(4 * (v + 1)), DeviceBuffer(4 * v * degree), DeviceBuffer(4),
+                DeviceBuffer(4 * v)]
+        wsb = B.hop_distances_workspace(v)
+        ws = DeviceBuffer(wsb)
+        try:
+            for b, a in zip(bufs, (off, c.reshape(-1), [s])):
+                b.upload(np.asarray(a, np.uint32))
+            times = []
+            for _ in range(4):
+                with timer:
+                    B.hop_distances(bufs[0].ptr, bufs[1].ptr, v, v * degree, bufs[2].ptr, 1, NEVER,
+                                    bufs[3].ptr, ws.ptr, wsb, timer.handle)
+                times.append(timer.ms)
+            ms.append(min(times[1:]))
+            hops.append(bufs[3].download(0, 4 * v).view(np.uint32))
+        finally:
+            for b in bufs + [ws]:
+                b.free()
+    timer.close()
+    print(f"[hops] by community {ms[0]:.2f} ms, at random {ms[1]:.2f} ms", flush=True)
+    assert np.array_equal(hops[0], hops[1][to])
+    assert ms[0] <= 2 * ms[1], ms
