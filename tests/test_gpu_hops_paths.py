@@ -147,3 +147,17 @@ def test_time_does_not_depend_on_the_numbering():
     print(f"[hops] by community {ms[0]:.2f} ms, at random {ms[1]:.2f} ms", flush=True)
     assert np.array_equal(hops[0], hops[1][to])
     assert ms[0] <= 2 * ms[1], ms
+
+
+@pytest.mark.parametrize("v,workgroups", [(2048, 1), (5000, 2), (40_000, 1), (40_000, 7),
+                                          (300_000, 1), (300_000, 50)])
+def test_fewer_workgroups_than_chunks(v, workgroups):
+    """As when the device is busy: the workgroups that run draw the tickets of
+    those that never do."""
+    rng = np.random.default_rng(v)
+    deg = rng.integers(0, 8, v)
+    off = np.concatenate([[0], np.cumsum(deg)])
+    col = rng.integers(0, v, off[-1])
+    src = rng.integers(0, v, 5)
+    got = gpu_hops(off, col, src, probe=(workgroups, 1 << 22))
+    assert np.array_equal(got, hop_distances(off, col, src, None))
