@@ -8,7 +8,8 @@
 // a hipMemcpyAsync of the chunk's bytes from the agent's pinned host copy
 // into a staging slot of the module, then the pool's unpack kernel
 // (k_copy<false>) scattering the slot into the destination units.  A small
-// chunk's unpack reads the host copy itself, without copy command and slot.
+// chunk's unpack reads the host copy itself, without copy command and slot,
+// unless its planes are tiny.
 //
 // The preemption signal is checked before every chunk: when a queued task
 // has a strictly smaller distance than the running one, the running task
@@ -64,10 +65,18 @@ struct Task {
 
 // Chunks of at most this many bytes are unpacked straight from the host copy:
 // one launch instead of a copy, two events and a launch.  Per chunk, copied /
-// straight: 128 KiB 19.9 / 10.4 us, 512 KiB 25.8 / 16.1, 1 MiB 34.1 / 27.1, 2 MiB
-// 52.4 / 44.4 (52.2 in 64 planes); larger ones gain less than a tenth, and the
-// copy engines leave the compute units alone.
+// straight, in pieces of 32 KiB: 256 KiB 24.8 / 19.3 us, 512 KiB 25.7 / 19.8, 1 MiB
+// 35.1 / 27.4, 2 MiB 53.1 / 44.6 (1 KiB pieces, the slowest: 53.1 / 55.4); larger
+// ones gain less than a tenth, and the copy engines leave the compute units
+// alone.
 constexpr u64 kDirectChunk = 2u << 20;
+// But not where a chunk falls into many tiny pieces (a plane's bytes of a unit,
+// at most 32 KiB): each is a read of its own over the link, of 2.6 ns at best.  16
+// bytes a piece: 32 KiB 18.2 / 11.7 us, 128 KiB 22.4 / 27.3, 512 KiB 34.9 / 89.7, 2
+// MiB 87.7 / 345; 32 bytes: 128 KiB 19.3 / 19.2, 512 KiB 27.1 / 57.4; 64 bytes: 128
+// KiB 21.3 / 12.0, 512 KiB 25.5 / 32.6; 128 bytes: 512 KiB 25.5 / 19.3, 2 MiB 53.2 /
+// 59.8; 256 bytes: 1 MiB 35.3 / 25.9, 2 MiB 53.2 / 44.6.
+constexpr u64 kDirectPieces = 4096, kDirectPiece = 256;
 
 typedef std::tuple<uint32_t, uint32_t, uint32_t> Key;   // (distance, agent, module)
 typedef std::pair<uint32_t, uint32_t> Id;                // (module, agent)
@@ -388,7 +397,9 @@ ss_status ss_loader_pump(ss_loader* L, uint32_t max_chunks, ss_load_log* log, ui
         C.chunk_bytes = m.d_chunk_bytes;
         C.unit_bytes = m.unit_bytes;
         C.capacity = m.U;
-        if (bytes <= kDirectChunk && m.host_dev &&
+        const u64 pieces = (u64)cnt * m.n_items;
+        if (bytes <= kDirectChunk && (pieces <= kDirectPieces || bytes >= pieces * kDirectPiece) &&
+            m.host_dev &&
             (reinterpret_cast<uintptr_t>(m.host_dev) + from) % 16 == 0) {
             // a small chunk: the unpack reads the host copy over the link itself
             C.staging = m.host_dev + from;

@@ -2,6 +2,7 @@
 copies (k_link) and the loader's unpack straight from the host copy, against the
 oracle at the sizes where they can go wrong."""
 import ctypes as C
+import time
 
 import numpy as np
 import pytest
@@ -235,4 +236,46 @@ def test_offset_lists_only_where_they_serve(form, lists):
         plain = 4 * 4 * capacity                # the plan's unit lists, whatever the form
         assert used >= plain + 16 * capacity if lists else used < plain + 8 * capacity, used
     finally:
+        mem.free()
+
+
+@pytest.mark.parametrize("chunks,slot_units", [
+    ([16] * 256, 16), ([16] * 256, 17), ([256] * 256, 17), ([240] * 256, 17)])
+def test_loader_chunks_of_small_planes(chunks, slot_units):
+    """4,096 pieces a chunk and more, of 256 bytes and less."""
+    test_loader_chunks(chunks, slot_units)
+
+
+def test_loader_time_of_tiny_planes():
+    """Chunks of many tiny planes take no longer than copied ones, which chunks
+    off the 16-byte grid always are (by reads over the link they took 2.6 times as
+    long)."""
+    units, slot_units = np.full(4, 4096, np.uint32), 256
+    spec = W.PoolSpec("kv", int(units.sum()), [16] * 64, units)
+    mem = PoolMemory(spec, 2 * 4 * slot_units * spec.unit_bytes, 4)
+    mem.host_np[:] = 1
+    to = np.random.default_rng(0).permutation(int(units.sum())).astype(np.int32)
+    d_to = DeviceBuffer(to.nbytes)
+    d_to.upload(to)
+    ms = []
+    try:
+        for shift in (0, 8):
+            args = mem.desc_args()
+            args["host_off"] = mem.host_off + np.uint64(shift)
+            args["host_off"][-1] = 0
+            loader = B.Loader([args])
+            times = []
+            for _ in range(5):
+                loader.sync()
+                t0 = time.perf_counter()
+                loader.submit([(0, a, 5, d_to.ptr + 4 * 4096 * a) for a in range(3)])
+                loader.pump(10_000)
+                loader.sync()
+                times.append(time.perf_counter() - t0)
+            loader.close()
+            ms.append(1e3 * min(times))
+        print(f"[loader] tiny planes {ms[0]:.2f} ms, copied {ms[1]:.2f} ms", flush=True)
+        assert ms[0] <= 1.5 * ms[1]
+    finally:
+        d_to.free()
         mem.free()
