@@ -80,8 +80,8 @@ struct ObjArgs {
     ObjCarry* carry;                  // [blocks]
     unsigned* coord;                  // [blocks + 1] rows consumed at each block boundary
     unsigned* w;                      // [N] 0 if active, else distance + 1, at most kNone
-    unsigned* odd;                    // [odd_n] per workgroup that wrote w: it met a distance of
-    unsigned odd_n;                   // kNone - 1, whose w is that of kNone
+    unsigned* odd;                    // [odd_n] per workgroup that wrote w, a byte per wave: it met
+    unsigned odd_n;                   // a distance of kNone - 1, whose w is that of kNone
 };
 
 // Merge-path coordinate (rows consumed) at diagonal d: the first p in
@@ -123,9 +123,10 @@ __device__ unsigned group_path_search(const unsigned* __restrict__ off, unsigned
 // else D[a] + 1, so that k_obj_min gathers one 32-bit word per reference that
 // carries both the distance and the activity.  The two largest distances
 // share a word; in the odd case that the smaller one occurs, k_obj_min reads
-// the distances of those agents again.  (With 64-bit words, which need no such
-// care, the gathers miss the L1 more often and this kernel writes twice as
-// much: 8 M agents and 56 M references 302 us a call, 278 us so.)
+// the distances of those agents again.  (64-bit words need no such care, but
+// the gathers miss the L1 more often and this kernel writes twice as much.  A
+// call by those and so: 8 M agents and 56 M references 297 and 273 us, 2 M
+// agents 63.9 and 60.6, 6,000 12.6 and 12.5, 300 10.5 and 10.5.)
 __global__ void __launch_bounds__(256) k_obj_prep(ObjArgs A, unsigned n_bounds,
                                                   unsigned part_blocks) {
     if (blockIdx.x < part_blocks) {
@@ -137,7 +138,8 @@ __global__ void __launch_bounds__(256) k_obj_prep(ObjArgs A, unsigned n_bounds,
         return;
     }
     // 2048 agents per block and round, eight per thread, loads before stores;
-    // four at a time where the arrays allow it
+    // four at a time where the arrays allow it (this kernel on 6,000 agents: 3.5 us
+    // with four only in whole rounds, 2.6 so)
     const unsigned blk = blockIdx.x - part_blocks;
     const u64 stride = (u64)(gridDim.x - part_blocks) * 2048u;
     bool odd = false;
@@ -148,18 +150,30 @@ __global__ void __launch_bounds__(256) k_obj_prep(ObjArgs A, unsigned n_bounds,
     const bool wide = ((reinterpret_cast<uintptr_t>(A.dist) | reinterpret_cast<uintptr_t>(A.w)) & 15) == 0 &&
                       (reinterpret_cast<uintptr_t>(A.active) & 3) == 0;
     for (u64 base = (u64)blk * 2048u; base < A.N; base += stride) {      // workgroup-uniform
-        if (wide && base + 2048 <= A.N) {
-            const u64 q = base / 4 + threadIdx.x;
-            const uint4 d0 = reinterpret_cast<const uint4*>(A.dist)[q];
-            const uint4 d1 = reinterpret_cast<const uint4*>(A.dist)[q + 256];
-            const unsigned a0 = reinterpret_cast<const unsigned*>(A.active)[q];
-            const unsigned a1 = reinterpret_cast<const unsigned*>(A.active)[q + 256];
-            auto four = [&](uint4 d, unsigned a) {
-                return make_uint4(word(d.x, a & 0xFFu), word(d.y, a & 0xFF00u),
-                                  word(d.z, a & 0xFF0000u), word(d.w, a & 0xFF000000u));
-            };
-            reinterpret_cast<uint4*>(A.w)[q] = four(d0, a0);
-            reinterpret_cast<uint4*>(A.w)[q + 256] = four(d1, a1);
+        if (wide) {
+            const u64 n4 = A.N / 4;
+            uint4 d[2];
+            unsigned a[2];
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const u64 q = base / 4 + threadIdx.x + k * 256u;
+                d[k] = make_uint4(0, 0, 0, 0);
+                a[k] = 0;
+                if (q < n4) {
+                    d[k] = reinterpret_cast<const uint4*>(A.dist)[q];
+                    a[k] = reinterpret_cast<const unsigned*>(A.active)[q];
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const u64 q = base / 4 + threadIdx.x + k * 256u;
+                if (q < n4)
+                    reinterpret_cast<uint4*>(A.w)[q] = make_uint4(
+                        word(d[k].x, a[k] & 0xFFu), word(d[k].y, a[k] & 0xFF00u),
+                        word(d[k].z, a[k] & 0xFF0000u), word(d[k].w, a[k] & 0xFF000000u));
+            }
+            const u64 rest = n4 * 4 + threadIdx.x;   // the last one to three agents
+            if (base + 2048 > rest && rest < A.N) A.w[rest] = word(A.dist[rest], A.active[rest] != 0);
             continue;
         }
         unsigned dv[8];
@@ -180,8 +194,9 @@ __global__ void __launch_bounds__(256) k_obj_prep(ObjArgs A, unsigned n_bounds,
             if (a < A.N) A.w[a] = word(dv[k], ac[k] != 0);
         }
     }
-    const int any = __syncthreads_or(odd);
-    if (threadIdx.x == 0) A.odd[blk] = any != 0;
+    const u64 any = __ballot(odd);                   // a byte per wave
+    if (__lane_id() == 0)
+        reinterpret_cast<unsigned char*>(A.odd + blk)[threadIdx.x >> 6] = any != 0;
 }
 
 // Persistent workgroups: the grid is a multiple of the eight XCDs, and
@@ -199,15 +214,16 @@ __global__ void __launch_bounds__(kObjThreads) k_obj_min(ObjArgs A, unsigned n_t
     __shared__ unsigned s_outd[kObjTile];     // rows ending in the block: min
     __shared__ unsigned char s_flag[kObjTile];
     __shared__ unsigned s_bmin, s_bact;
+    __shared__ unsigned s_odd[kObjThreads / 64];
+    static_assert(kObjThreads == 256, "four waves");
 
     constexpr unsigned kXcds = 8;
     const unsigned tid = threadIdx.x;
     const unsigned total = A.M + A.R;
-    // any flag set: see k_obj_prep.  The first read stands outside the loop, so
-    // that it is in flight with the tile's own reads (324,160 references of small
-    // trees, a call: 14.5 us with every read in the loop, 14.4 so).
-    unsigned flags = __lane_id() < A.odd_n ? A.odd[__lane_id()] : 0u;
-    for (unsigned k = __lane_id() + 64; k < A.odd_n; k += 64) flags |= A.odd[k];
+    // any flag set: see k_obj_prep.  The workgroup's waves read a part each, used
+    // only once the first tile is staged, so that the reads cost no round trip.
+    unsigned flags = tid < A.odd_n ? A.odd[tid] : 0u;
+    for (unsigned k = tid + kObjThreads; k < A.odd_n; k += kObjThreads) flags |= A.odd[k];
     const unsigned xcd = blockIdx.x % kXcds, per_xcd = gridDim.x / kXcds;
     const unsigned q = n_tiles / kXcds, rem = n_tiles % kXcds;
     const unsigned t_lo = xcd < rem ? xcd * (q + 1) : rem * (q + 1) + (xcd - rem) * q;
@@ -235,7 +251,6 @@ __global__ void __launch_bounds__(kObjThreads) k_obj_min(ObjArgs A, unsigned n_t
         }
         // one word per reference: e = 0 if the agent is active, else D + 1
         unsigned char act[kObjItems];
-        const bool odd = __ballot(flags != 0) != 0;
     #pragma unroll
         for (int k = 0; k < kObjItems; ++k) {
             const unsigned i = tid + k * kObjThreads;
@@ -246,7 +261,7 @@ __global__ void __launch_bounds__(kObjThreads) k_obj_min(ObjArgs A, unsigned n_t
                 if (a < A.N) {
                     const unsigned e = A.w[a];
                     act[k] = e == 0;
-                    val[k] = e == 0 ? 0u : e != kNone ? e - 1 : odd ? A.dist[a] : kNone;
+                    val[k] = e != kNone ? max(e, 1u) - 1 : kNone;
                 }
             }
         }
@@ -256,7 +271,19 @@ __global__ void __launch_bounds__(kObjThreads) k_obj_min(ObjArgs A, unsigned n_t
             if (i < nrow + nref) s_item[i] = val[k];
             if (i >= nrow && i < nrow + nref) s_flag[i] = act[k];
         }
+        const u64 any = __ballot(flags != 0);
+        if (__lane_id() == 0) s_odd[tid >> 6] = any != 0;
         __syncthreads();
+        if (s_odd[0] | s_odd[1] | s_odd[2] | s_odd[3]) {          // workgroup-uniform
+            // kNone may stand for kNone - 1: such agents' distances themselves
+#pragma unroll 1
+            for (unsigned i = tid; i < nrow + nref; i += kObjThreads) {
+                if (i < nrow || s_item[i] != kNone) continue;
+                const unsigned a = A.agents[r0 + (i - nrow)];
+                if (a < A.N) s_item[i] = A.dist[a];
+            }
+            __syncthreads();
+        }
 
         // this thread's start on the block's merge path (binary search in LDS)
         const unsigned k0 = tid * (unsigned)kObjItems;

@@ -49,3 +49,42 @@ def test_words(n, shift, odd):
     finally:
         for b in bufs + [d_dist, d_act, d_out, d_oa, ws]:
             b.free()
+
+
+@pytest.mark.parametrize("n", [2, 3, 4, 5, 2046, 2050, 300_003, 1_060_001])
+def test_last_agents(n):
+    """The one to three agents that no four-agent read takes, and the flags of many
+    preparing workgroups (518 in the last case): only the last agent, or the last
+    of a wave, has the second largest distance."""
+    rng = np.random.default_rng(n)
+    base = rng.choice(np.array([5, S - 2, S], np.uint32), n)
+    act = np.zeros(n, np.uint8)
+    act[rng.integers(0, n, n // 10)] = 1
+    some = np.unique(np.concatenate([np.arange(max(0, n - 6), n), rng.integers(0, n, 500)]))
+    never = np.flatnonzero(base == S)[:3000]
+    lists = [[a] for a in some] + [never.tolist(), never[-4:].tolist() + [n - 1], []]
+    off = np.concatenate([[0], np.cumsum([len(x) for x in lists])]).astype(np.uint32)
+    agents = np.concatenate([np.asarray(x, np.uint32) for x in lists])
+    m = len(lists)
+    bufs = [DeviceBuffer(b) for b in (off.nbytes, agents.nbytes, 4 * n, n, 4 * m, m)]
+    wsb = B.object_distances_workspace(m, len(agents), n)
+    ws = DeviceBuffer(wsb)
+    try:
+        bufs[0].upload(off)
+        bufs[1].upload(agents)
+        for at in (None, n - 1, min(n - 1, 63 * 4 + 3)):
+            dist = base.copy()
+            if at is not None:
+                dist[at] = S - 1
+                act[at] = 0
+            bufs[2].upload(dist)
+            bufs[3].upload(act)
+            ws.upload(np.full(wsb, 0x77, np.uint8))
+            B.object_distances(bufs[0].ptr, bufs[1].ptr, m, len(agents), bufs[2].ptr, bufs[3].ptr, n,
+                               bufs[4].ptr, bufs[5].ptr, ws.ptr, wsb)
+            exp_d, exp_a = object_distances(off, agents, dist, act)
+            assert np.array_equal(bufs[4].download(0, 4 * m).view(np.uint32), exp_d), at
+            assert np.array_equal(bufs[5].download(0, m), exp_a), at
+    finally:
+        for b in bufs + [ws]:
+            b.free()
