@@ -1702,11 +1702,13 @@ ss_status hop_call(const uint32_t* row_off, const uint32_t* col, uint32_t n_vert
     // per CU: more workgroups expand faster, but all of them add to and poll one
     // counter per level (200,000 vertices: 196 chunks 97 us, 98 chunks 86 us;
     // 50,000: 25 chunks 79 us, 49 chunks 64 us; 1 M: 1,024 chunks of a quarter
-    // of the threads 817 us, 256 chunks 212 us)
+    // of the threads 817 us, 256 chunks 212 us); fewer vertices where a chunk
+    // would have more than 2^17 edges (20,000 of degree 500: 1,775 us by 20 chunks,
+    // 961 us by 76)
     const u64 V = n_vertices;
-    A.chunks = (unsigned)std::min<u64>(
-        std::max((V + 4095) / 4096, std::min<u64>((V + 1023) / 1024, 96)),
-        std::min<unsigned>(kBfsMost, std::max(cus, 1)));
+    const u64 want = std::max({(V + 4095) / 4096, std::min<u64>((V + 1023) / 1024, 96),
+                               std::min<u64>((V + 63) / 64, n_edges >> 17)});
+    A.chunks = (unsigned)std::min<u64>(want, std::min<unsigned>(kBfsMost, std::max(cus, 1)));
     hipLaunchKernelGGL(k_bfs_init, dim3((n_vertices + kBfsThreads - 1) / kBfsThreads),
                        dim3(kBfsThreads), 0, st, A);
     hipError_t e = hipGetLastError();

@@ -161,3 +161,15 @@ def test_fewer_workgroups_than_chunks(v, workgroups):
     src = rng.integers(0, v, 5)
     got = gpu_hops(off, col, src, probe=(workgroups, 1 << 22))
     assert np.array_equal(got, hop_distances(off, col, src, None))
+
+
+@pytest.mark.parametrize("v,degree", [(70, 8000), (1000, 1000), (2100, 300)])
+def test_dense_graphs(v, degree):
+    """Chunks of fewer than 1,024 vertices, down to one stretch of 64."""
+    rng = np.random.default_rng(v)
+    off = np.arange(v + 1) * degree
+    # most edges stay near, so that the search takes some levels
+    col = (np.arange(v)[:, None] + rng.integers(0, 9, (v, degree))) % v
+    col[:, 0] = rng.integers(0, v, v)
+    got = gpu_hops(off, col.reshape(-1), [v // 3])
+    assert np.array_equal(got, hop_distances(off, col.reshape(-1), np.array([v // 3]), None))
