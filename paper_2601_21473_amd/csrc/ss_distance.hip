@@ -61,6 +61,7 @@ constexpr int kObjThreads = 256;
 constexpr int kObjItems = 8;                          // merge items per thread
 constexpr int kObjTile = kObjThreads * kObjItems;     // merge items per workgroup
 constexpr unsigned kNone = 0xFFFFFFFFu;
+constexpr unsigned kShared = kNone - 2;               // its agent word is also that of kNone - 1
 
 struct ObjCarry {
     unsigned row;      // object, or kNone
@@ -79,9 +80,9 @@ struct ObjArgs {
     unsigned char* out_act;           // [M]
     ObjCarry* carry;                  // [blocks]
     unsigned* coord;                  // [blocks + 1] rows consumed at each block boundary
-    unsigned* w;                      // [N] 0 if active, else distance + 1, at most kNone
+    unsigned* w;                      // [N] 0 if active, else distance + 1; kNone for kNone
     unsigned* odd;                    // [odd_n] per workgroup that wrote w, a byte per wave: it met
-    unsigned odd_n;                   // a distance of kNone - 1, whose w is that of kNone
+    unsigned odd_n;                   // a distance of kNone - 1, whose w is that of kShared
 };
 
 // Merge-path coordinate (rows consumed) at diagonal d: the first p in
@@ -121,9 +122,10 @@ __device__ unsigned group_path_search(const unsigned* __restrict__ off, unsigned
 // merge-path coordinate of every workgroup boundary b * kObjTile,
 // b = 0..blocks (16 per block).  The rest: w[a] = 0 if agent a is active,
 // else D[a] + 1, so that k_obj_min gathers one 32-bit word per reference that
-// carries both the distance and the activity.  The two largest distances
-// share a word; in the odd case that the smaller one occurs, k_obj_min reads
-// the distances of those agents again.  (64-bit words need no such care, but
+// carries both the distance and the activity.  That is a value too many: the
+// two distances below 0xFFFFFFFF (which is common: never) share a word, and in
+// the odd case that the larger one occurs, k_obj_min reads the distances of the
+// agents with that word again.  (64-bit words need no such care, but
 // the gathers miss the L1 more often and this kernel writes twice as much.  A
 // call by those and so: 8 M agents and 56 M references 297 and 273 us, 2 M
 // agents 63.9 and 60.6, 6,000 12.6 and 12.5, 300 10.5 and 10.5.)
@@ -145,7 +147,7 @@ __global__ void __launch_bounds__(256) k_obj_prep(ObjArgs A, unsigned n_bounds,
     bool odd = false;
     auto word = [&](unsigned d, bool act) {
         odd |= !act && d == kNone - 1;
-        return act ? 0u : d < kNone - 1 ? d + 1 : kNone;
+        return act ? 0u : d == kNone ? kNone : min(d, kShared) + 1;
     };
     const bool wide = ((reinterpret_cast<uintptr_t>(A.dist) | reinterpret_cast<uintptr_t>(A.w)) & 15) == 0 &&
                       (reinterpret_cast<uintptr_t>(A.active) & 3) == 0;
@@ -275,10 +277,10 @@ __global__ void __launch_bounds__(kObjThreads) k_obj_min(ObjArgs A, unsigned n_t
         if (__lane_id() == 0) s_odd[tid >> 6] = any != 0;
         __syncthreads();
         if (s_odd[0] | s_odd[1] | s_odd[2] | s_odd[3]) {          // workgroup-uniform
-            // kNone may stand for kNone - 1: such agents' distances themselves
+            // kShared may stand for kNone - 1: such agents' distances themselves
 #pragma unroll 1
             for (unsigned i = tid; i < nrow + nref; i += kObjThreads) {
-                if (i < nrow || s_item[i] != kNone) continue;
+                if (i < nrow || s_item[i] != kShared) continue;
                 const unsigned a = A.agents[r0 + (i - nrow)];
                 if (a < A.N) s_item[i] = A.dist[a];
             }
