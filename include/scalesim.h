@@ -173,10 +173,11 @@ typedef struct {                    /* cumulative since create or ss_reset_stats
     double   plan_phase_us[7];             /* plan phases up to the published plan
                                               (classify; the histogram cuts and the sorts
                                               of the evictable, demand and candidate sets
-                                              with their unit prefixes; demand victims;
-                                              the acceptance's LDS copy of the evictable
-                                              prefix; acceptance; lists; the result and
-                                              its publication); classify runs
+                                              with their unit prefixes; demand victims,
+                                              and where the sorted sets don't fit LDS the
+                                              evictable ones' copy there; nothing, as that
+                                              copy once stood here; acceptance; lists; the
+                                              result and its publication); classify runs
                                               from the plan kernel's entry (its first
                                               workgroup when N > 12288).  The free-unit
                                               pick and the block-table update follow in

@@ -967,12 +967,18 @@ __device__ __forceinline__ void bt_tail(const BtArgs* Bp, unsigned n_v, unsigned
 
 // Publish the plan to the host: one thread writes the plan's sequence number to
 // the mapped flag word, which the host polls, once every thread's host-visible
-// writes are complete.  Those are system-scope stores (host_store), which no
-// cache holds back, so each wave waits for its own and nothing is flushed: a
-// system-scope release would write back the whole L2, this plan's lists for
-// the device among it (publication at 64 agents 2.7 us so, 0.8 us
-// without).
-__device__ __forceinline__ void publish_plan(const PlanArgs& A) {
+// writes are complete.  Those of a plan of up to kStoredItems victims and loads
+// are system-scope stores (host_store), which no cache holds back, so each wave
+// waits for its own and nothing is flushed: a system-scope release would write
+// back the whole L2, this plan's lists for the device among it.  But every such
+// store goes its own way, so longer lists are written by plain stores and
+// released.  Lists and publication by plain stores / by system-scope ones: 196
+// items 5.0 / 2.9 us, 949 5.5 / 4.1, 1,935 6.4 / 5.8, 3,538 8.2 / 9.2, 5,701 10.9 /
+// 14.2, 32,614 45 / 63.  (The fence only releases: nothing after it reads what
+// the host writes.)
+constexpr unsigned kStoredItems = 2048;
+__device__ __forceinline__ void publish_plan(const PlanArgs& A, unsigned items) {
+    if (items > kStoredItems) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (threadIdx.x == 0)
@@ -1071,7 +1077,7 @@ __device__ __forceinline__ void plan_core(const PlanArgs& A, u64* lds, CoreShare
             host_store(A.res_host, r);
             if (kMode == kMany) *A.cnt = PlanCounters{};
         }
-        publish_plan(A);
+        publish_plan(A, 0);
         stamp(8);
         return;
     }
@@ -1316,11 +1322,16 @@ __device__ __forceinline__ void plan_core(const PlanArgs& A, u64* lds, CoreShare
             n_v = min(nT, n_d + 1 + (unsigned)tot);
         }
         const unsigned n_l = nL + n_p;
+        const bool stored = n_v + n_l <= kStoredItems;       // block-uniform
+        auto put = [&](auto* p, auto v) {
+            if (stored) host_store(p, v);
+            else *p = v;
+        };
 
         // plan lists, load offsets, residency (victims and loads are disjoint)
         for (unsigned i = tid; i < n_l; i += blockDim.x) {
             const unsigned a = (unsigned)((i < nL ? L[i] : C[i - nL]) & idmask);
-            host_store(A.loads_host + i, a);
+            put(A.loads_host + i, a);
             A.loads[i] = a;
             A.resident[a] = 1;
             if (i >= nL) A.loff[i + 1] = c.sum_demand + pc[i - nL + 1];
@@ -1331,8 +1342,8 @@ __device__ __forceinline__ void plan_core(const PlanArgs& A, u64* lds, CoreShare
         auto victim = [&](unsigned i, u64* wunits) {
             const unsigned v = (unsigned)(E[nT - 1 - i] & idmask);
             const unsigned char w = (!A.dirty || A.dirty[v]) ? 1 : 0;
-            host_store(A.victims_host + i, v);
-            host_store(A.vwritten_host + i, w);
+            put(A.victims_host + i, v);
+            put(A.vwritten_host + i, w);
             A.victims[i] = v;
             A.vwritten[i] = w;
             A.resident[v] = 0;
@@ -1387,7 +1398,7 @@ __device__ __forceinline__ void plan_core(const PlanArgs& A, u64* lds, CoreShare
         host_store(A.res_host, r);
         if (kMode == kMany) *A.cnt = PlanCounters{};
     }
-    publish_plan(A);
+    publish_plan(A, n_v + n_l);
     stamp(7);
     // The host has the plan; the workgroup goes on to pick the pre-step free
     // units (ascending) and to update the block table (waves over victims,

@@ -52,3 +52,23 @@ def test_joint_sort_edge(n):
     tr = W.Trace(f"joint{n}", n, 4, [pool], active, dist, dist.copy(), {})
     run_parity(tr, theta=S, slot_units=8192, ring_slots=2, sample_units=4000,
                label=f"joint sort edge {n}")
+
+
+@pytest.mark.parametrize("first", [2047, 2048, 2049])
+def test_published_list_lengths(first):
+    """Plans of 2,048 victims and loads (written to the host by system-scope
+    stores), one more and one less, in one step and over victims and loads."""
+    n = 6000
+    active = np.zeros((5, n), np.uint8)
+    active[0, :first] = 1
+    for t, k in enumerate((1023, 1024, 1025)):
+        active[t + 1, 2100 + 1100 * t:2100 + 1100 * t + k] = 1
+    cap = first + 1
+    active[4, 3000:3000 + cap] = 1
+    dist = W.exact_distances(active)
+    pool = W.PoolSpec("syn", cap, [16], np.ones(n, np.uint32))
+    tr = W.Trace(f"lists{first}", n, 5, [pool], active, dist, dist.copy(), {})
+    mask = (np.random.default_rng(first).random((5, n)) < 0.5).astype(np.uint8)
+    for theta in (0, S):
+        run_parity(tr, theta=theta, slot_units=8192, ring_slots=2, dirty=mask, check_mirrors=True,
+                   label=f"lists {first}, threshold {theta}")
