@@ -1322,7 +1322,8 @@ __device__ __forceinline__ void plan_core(const PlanArgs& A, u64* lds, CoreShare
             n_v = min(nT, n_d + 1 + (unsigned)tot);
         }
         const unsigned n_l = nL + n_p;
-        const bool stored = n_v + n_l <= kStoredItems;       // block-uniform
+        static_assert(kCoreThreads <= kStoredItems, "a small plan's lists are short");
+        const bool stored = kMode == kSmall || n_v + n_l <= kStoredItems;    // block-uniform
         auto put = [&](auto* p, auto v) {
             if (stored) host_store(p, v);
             else *p = v;
@@ -1398,7 +1399,7 @@ __device__ __forceinline__ void plan_core(const PlanArgs& A, u64* lds, CoreShare
         host_store(A.res_host, r);
         if (kMode == kMany) *A.cnt = PlanCounters{};
     }
-    publish_plan(A, n_v + n_l);
+    publish_plan(A, kMode == kSmall ? 0 : n_v + n_l);
     stamp(7);
     // The host has the plan; the workgroup goes on to pick the pre-step free
     // units (ascending) and to update the block table (waves over victims,
