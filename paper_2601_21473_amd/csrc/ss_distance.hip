@@ -45,8 +45,9 @@
 //   k_pair      all pairs in one launch (few agents): per pair a packed 16-bit
 //               subtract and a 16-bit dot product give dx^2 + dy^2 exactly.
 //   k_near_*    many agents: sorted into cells, each looks only at the cells
-//               about it (50,000 agents: 206 us by all pairs, 40 us; 200,000:
-//               3,330 and 52 us).
+//               about it (uniform on 2,048 x 2,048 tiles: 50,000 agents 205 us
+//               by all pairs, 45 so; 200,000 3,280 and 54; gathered about 400
+//               places on 8,192 x 8,192 tiles 200,000 take 81).
 // Both are plain integer ALU work (no contraction), so no MFMA.
 #include "scalesim.h"
 #include "ss_internal.h"
@@ -584,8 +585,12 @@ __global__ void __launch_bounds__(kBfsThreads) k_bfs(BfsArgs A) {
 }
 
 // Graphs of more than kBfsSweep vertices: frontier queues instead of sweeps over
-// all vertices, whose cost per level grows with them (16 M vertices, one at
-// every level: 30.7 us a level by sweeps, 13.3 by queues; 4 M: 10.5 and 13.3).
+// all vertices, whose cost per level grows with them.  By queues / by sweeps, a
+// level that reaches one vertex: 4.2 M vertices 11.5 / 9.7 us, 6 M 12.1 / 14.8, 8 M
+// 11.4 / 18.1, 16 M 15.3 / 31.0.  A shallow search gains by sweeps at any size
+// (random graphs of degree 8, 5 to 11 levels: 4.2 M 1,226 / 778 us, 8 M 2,082 /
+// 1,542, 16 M 3,833 / 3,105), but how deep a graph is shows only in the search,
+// and a deep one loses the more the larger it is.
 constexpr unsigned kBfsSweep = 1u << 22;
 constexpr int kQueueThreads = 256;
 constexpr int kQueueEdges = 8;               // edges claimed per vertex per round
