@@ -208,6 +208,17 @@ def test_estimator_argument_checks():
     assert L.ss_interaction_distances(*it()) == B.SS_ERR_ARG
 
 
+def test_hop_probe_argument_checks():
+    L = B.load()
+    V = C.c_void_p
+    args = [V(256), V(512), 4, 8, V(1024), 1, 0xFFFFFFFF, V(2048), V(4096), 1 << 20]
+    assert L.ss_probe_hop_distances(*args, 0, 1) == B.SS_ERR_ARG
+    assert "workgroups" in L.ss_last_error().decode()
+    assert L.ss_probe_hop_distances(*args, 1, 1) == B.SS_ERR_ARG         # host addresses
+    args[2] = 0
+    assert L.ss_probe_hop_distances(*args, 1, 1) == B.SS_OK              # nothing to do
+
+
 def test_stream_event_argument_checks():
     L = B.load()
     assert L.ss_stream_create(None) == B.SS_ERR_ARG
